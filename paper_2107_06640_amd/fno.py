@@ -37,8 +37,19 @@ def _lib():
         lib.fno_adam.argtypes = [i64, P, P, P, P, f32, f32, f32, f32, C.c_int, P]
         lib.fno_rel_l2.argtypes = [i64, i64, P, P, P, P, P]
         lib.fno_scale.argtypes = [i64, P, f32, P]
+        lib.fno_fused_shape.argtypes = [i64] * 7
+        lib.fno_pointwise.argtypes = [i64, i64, i64, P, P, P, P, P]
+        lib.fno_head.argtypes = [i64, i64, i64, P, P, P, P, P, P, P]
+        lib.fno_head_backward.argtypes = [i64, i64, i64] + [P] * 10
+        lib.fno_layer_backward.argtypes = [i64, i64, i64] + [P] * 7
+        lib.fno_dft_ty.argtypes = [i64, i64, i64, i64, P, P, i64, i64, P, P, i64, i64, P, P]
+        lib.fno_dft_x.argtypes = [i64, i64, i64, i64, C.c_int, P, P, i64, i64, P, P, P]
+        lib.fno_mix.argtypes = [i64, i64, i64, P, P, i64, i64, C.c_int, P, P]
+        lib.fno_mix_grad.argtypes = [i64, i64, i64, P, P, P, P]
+        lib.fno_idft_yt.argtypes = [i64] * 6 + [P, P, P, i64, i64, P, i64, i64, P, i64, i64, P, P, P, P, C.c_int, P]
         for n in ("fno_gemm", "fno_bias_act", "fno_gelu_backward", "fno_channel_sum", "fno_adam", "fno_rel_l2",
-                  "fno_scale"):
+                  "fno_scale", "fno_fused_shape", "fno_pointwise", "fno_head", "fno_head_backward",
+                  "fno_layer_backward", "fno_dft_ty", "fno_dft_x", "fno_mix", "fno_mix_grad", "fno_idft_yt"):
             getattr(lib, n).restype = C.c_int
         lib._fno_declared = True
     return lib
@@ -87,6 +98,42 @@ class Kernels:
 
     def scale(self, x, s):
         _chk(self.lib.fno_scale(x.numel(), _p(x), s, self.stream), "fno_scale")
+
+    # -- fused stages (include/fno.h), for the shapes fused_shape accepts
+    def fused_shape(self, X, Y, T, cin, W, m, H):
+        return bool(self.lib.fno_fused_shape(X, Y, T, cin, W, m, H))
+
+    def pointwise(self, n, cout, cin, Wm, x, bias, z):
+        _chk(self.lib.fno_pointwise(n, cout, cin, _p(Wm), _p(x), _p(bias), _p(z), self.stream), "fno_pointwise")
+
+    def head(self, n, W, H, Q1, q1, Q2, q2, v, y):
+        _chk(self.lib.fno_head(n, W, H, _p(Q1), _p(q1), _p(Q2), _p(q2), _p(v), _p(y), self.stream), "fno_head")
+
+    def head_backward(self, n, W, H, Q1, q1, Q2, v, dy, dv, dQ1, dq1, dQ2):
+        _chk(self.lib.fno_head_backward(n, W, H, _p(Q1), _p(q1), _p(Q2), _p(v), _p(dy), _p(dv), _p(dQ1), _p(dq1),
+                                        _p(dQ2), self.stream), "fno_head_backward")
+
+    def layer_backward(self, n, cout, cin, z, da, x, dz, dW, db):
+        _chk(self.lib.fno_layer_backward(n, cout, cin, _p(z), _p(da), _p(x), _p(dz), _p(dW), _p(db), self.stream),
+             "fno_layer_backward")
+
+    def dft_ty(self, slices, Y, T, m, v, Bt, sBk, sBn, F0, F1, sFm, sFk, out):
+        _chk(self.lib.fno_dft_ty(slices, Y, T, m, _p(v), _p(Bt), sBk, sBn, _p(F0), _p(F1), sFm, sFk, _p(out),
+                                 self.stream), "fno_dft_ty")
+
+    def dft_x(self, batch, M, K, inner, inverse, A0, A1, sAm, sAk, x, out):
+        _chk(self.lib.fno_dft_x(batch, M, K, inner, 1 if inverse else 0, _p(A0), _p(A1), sAm, sAk, _p(x), _p(out),
+                                self.stream), "fno_dft_x")
+
+    def mix(self, B, W, nm, x, R, sRi, sRo, conj, out):
+        _chk(self.lib.fno_mix(B, W, nm, _p(x), _p(R), sRi, sRo, 1 if conj else 0, _p(out), self.stream), "fno_mix")
+
+    def mix_grad(self, B, W, nm, x, dY, dR):
+        _chk(self.lib.fno_mix_grad(B, W, nm, _p(x), _p(dY), _p(dR), self.stream), "fno_mix_grad")
+
+    def idft_yt(self, B, X, Y, T, m, W, V2, G0, G1, sGm, sGk, Bt, sBk, sBn, Wm, sWo, sWi, v, bias, z, a, act):
+        _chk(self.lib.fno_idft_yt(B, X, Y, T, m, W, _p(V2), _p(G0), _p(G1), sGm, sGk, _p(Bt), sBk, sBn, _p(Wm), sWo,
+                                  sWi, _p(v), _p(bias), _p(z), _p(a), 1 if act else 0, self.stream), "fno_idft_yt")
 
 
 def mode_indices(n, m):
@@ -140,6 +187,9 @@ class FNO:
         self.dev = device
         self.k = Kernels(stream) if kernels is None else kernels
         self.nm = (2 * modes) * (2 * modes) * modes
+        # the fused stages, where the kernels have them and take these sizes; else chains of general products
+        fits = getattr(self.k, "fused_shape", None)
+        self.fused = fits is not None and fits(X, Y, T, cin, width, modes, hidden)
         rng = np.random.default_rng(seed)
         W, m = width, modes
 
@@ -258,6 +308,39 @@ class FNO:
             k.gemm(nb, Y, m, 2 * m2, 1.0, F, 0, 0, 1, Y, dU2, 0, 2 * m2 * m, m, 1, 0.0, dU1, pi * m, Y * m2, m2, 1)
         k.gemm(1, rows, T, m2, 1.0, dU1, 0, 0, m2, 1, M["Ft"], 0, 0, 1, m2, 1.0, dv, 0, 0, T, 1)
 
+    # -- the same two maps in fused stages: transforms along t and y, along x, channel mixing, inverse along x,
+    # inverse along y and t with the pointwise product (and the bias and activation, forward) in the same pass
+    def _layer_fused(self, l, v, B, z, a, act):
+        """z, a (each may be None) = act(K_l v + W_l v + b_l); returns the kept modes of v."""
+        X, Y, T, W, m, nm = self.X, self.Y, self.T, self.W, self.m, self.nm
+        k, M, P, m2 = self.k, self.mats, self.params, 2 * self.m
+        U2 = self._empty(W * B * X * 2 * m2 * m)
+        k.dft_ty(W * B * X, Y, T, m, v, M["Ft"], m2, 1, M["Fy_re"], M["Fy_im"], Y, 1, U2)
+        U3 = self._empty(W * B * 2 * nm)
+        k.dft_x(W * B, 2 * m2, X, m2 * m, False, M["Fx_re"], M["Fx_im"], X, 1, U2, U3)
+        Ym = self._empty(W * B * 2 * nm)
+        k.mix(B, W, nm, U3, P[f"R{l}"], W, 1, False, Ym)
+        V2 = U2  # no longer needed
+        k.dft_x(W * B, X, 2 * m2, m2 * m, True, M["Gx_re"], M["Gx_im"], 2 * m2, 1, Ym, V2)
+        k.idft_yt(B, X, Y, T, m, W, V2, M["Gy_re"], M["Gy_im"], 2 * m2, 1, M["Gt"], T, 1, P[f"W{l}"], W, 1, v,
+                  P[f"b{l}"], z, a, act)
+        return U3
+
+    def _layer_fused_backward(self, l, U3, dz, B, dv):
+        """dv = K_l^T dz + W_l^T dz; the gradient of the mixing weights."""
+        X, Y, T, W, m, nm = self.X, self.Y, self.T, self.W, self.m, self.nm
+        k, M, P, m2 = self.k, self.mats, self.params, 2 * self.m
+        dV2 = self._empty(W * B * X * 2 * m2 * m)
+        k.dft_ty(W * B * X, Y, T, m, dz, M["Gt"], 1, T, M["Gy_re"], M["Gy_im"], 1, 2 * m2, dV2)
+        dYm = self._empty(W * B * 2 * nm)
+        k.dft_x(W * B, 2 * m2, X, m2 * m, False, M["Gx_re"], M["Gx_im"], 1, 2 * m2, dV2, dYm)
+        dU3 = self._empty(W * B * 2 * nm)
+        k.mix(B, W, nm, dYm, P[f"R{l}"], 1, W, True, dU3)
+        k.mix_grad(B, W, nm, U3, dYm, self.grads[f"R{l}"])
+        k.dft_x(W * B, X, 2 * m2, m2 * m, True, M["Fx_re"], M["Fx_im"], 1, X, dU3, dV2)
+        k.idft_yt(B, X, Y, T, m, W, dV2, M["Fy_re"], M["Fy_im"], 1, Y, M["Ft"], 1, m2, P[f"W{l}"], 1, W, dz, None,
+                  None, dv, False)
+
     # ------------------------------------------------------------------
     def forward(self, u, keep=False):
         """u: [Cin][B][X][Y][T] device tensor -> y [1][B][X][Y][T]."""
@@ -266,6 +349,22 @@ class FNO:
         W, k, P = self.W, self.k, self.params
         tape = {"u": u}
         v = self._empty(W * S)
+        if self.fused:
+            k.pointwise(S, W, self.cin, P["P"], u, P["p"], v)
+            for l in range(self.L):
+                act = l < self.L - 1
+                z = self._empty(W * S) if keep or not act else None
+                a = self._empty(W * S) if act else None
+                U3 = self._layer_fused(l, v, B, z, a, act)
+                if keep:
+                    tape[f"v{l}"], tape[f"z{l}"], tape[f"U{l}"] = v, z, U3
+                v = a if act else z
+            y = self._empty(S)
+            k.head(S, W, self.H, P["Q1"], P["q1"], P["Q2"], P["q2"], v, y)
+            if keep:
+                tape.update(vL=v, B=B)
+                self.tape = tape
+            return y.view(1, B, self.X, self.Y, self.T)
         self._pointwise(P["P"], u, v, self.cin, W, S)
         k.bias_act(1, W, S, v, P["p"], v, False)
         for l in range(self.L):
@@ -303,6 +402,17 @@ class FNO:
         W, H = self.W, self.H
         dy = dy.reshape(-1).contiguous()
         k.channel_sum(1, 1, S, dy, G["q2"])
+        if self.fused:
+            dv = self._empty(W * S)
+            k.head_backward(S, W, H, P["Q1"], P["q1"], P["Q2"], t["vL"], dy, dv, G["Q1"], G["q1"], G["Q2"])
+            for l in reversed(range(self.L)):
+                z = t[f"z{l}"] if l < self.L - 1 else None
+                k.layer_backward(S, W, W, z, dv, t[f"v{l}"], dv, G[f"W{l}"], G[f"b{l}"])
+                dvn = self._empty(W * S)
+                self._layer_fused_backward(l, t[f"U{l}"], dv, B, dvn)
+                dv = dvn
+            k.layer_backward(S, W, self.cin, None, dv, t["u"], None, G["P"], G["p"])
+            return G
         self._weight_grad(dy, t["g"], G["Q2"], 1, H, S)
         dg = self._empty(H * S)
         self._pointwise_t(P["Q2"], dy, dg, 1, H, S)
@@ -349,8 +459,8 @@ class FNO:
 
 
 class CountingKernels(Kernels):
-    """Kernels that also count the products' algorithmic flops (2 batch M N K per call)
-    and bytes (FP32 A and B read once, C read and written once)."""
+    """Kernels that also count the products' algorithmic flops (2 batch M N K per product)
+    and bytes (FP32 operands read once; the result written once, and read where it is added to)."""
 
     def __init__(self, stream=None):
         super().__init__(stream)
@@ -358,11 +468,52 @@ class CountingKernels(Kernels):
         self.bytes = 0
         self.calls = 0
 
-    def gemm(self, batch, M, N, K, *args, **kw):
-        self.flops += 2 * batch * M * N * K
-        self.bytes += 4 * batch * (M * K + K * N + 2 * M * N)
+    def _add(self, products, values):
+        """products: multiply-adds; values: FP32 values moved."""
+        self.flops += 2 * products
+        self.bytes += 4 * values
         self.calls += 1
+
+    def gemm(self, batch, M, N, K, *args, **kw):
+        self._add(batch * M * N * K, batch * (M * K + K * N + 2 * M * N))
         super().gemm(batch, M, N, K, *args, **kw)
+
+    def pointwise(self, n, cout, cin, *args):
+        self._add(n * cout * cin, n * (cout + cin))
+        super().pointwise(n, cout, cin, *args)
+
+    def head(self, n, W, H, *args):
+        self._add(n * H * (W + 1), n * (W + 1))
+        super().head(n, W, H, *args)
+
+    def head_backward(self, n, W, H, *args):
+        self._add(n * H * (3 * W + 2), n * (2 * W + 1))
+        super().head_backward(n, W, H, *args)
+
+    def layer_backward(self, n, cout, cin, z, *args):
+        self._add(n * cout * cin, n * (cout + cin + (0 if z is None else 2 * cout)))
+        super().layer_backward(n, cout, cin, z, *args)
+
+    def dft_ty(self, slices, Y, T, m, *args):
+        self._add(slices * (Y * 2 * m * T + 2 * 4 * m * m * Y), slices * (Y * T + 4 * m * m))
+        super().dft_ty(slices, Y, T, m, *args)
+
+    def dft_x(self, batch, M, K, inner, *args):
+        self._add(batch * 2 * M * K * inner, 3 * batch * max(M, K) * inner)
+        super().dft_x(batch, M, K, inner, *args)
+
+    def mix(self, B, W, nm, *args):
+        self._add(4 * nm * B * W * W, nm * (4 * B * W + 2 * W * W))
+        super().mix(B, W, nm, *args)
+
+    def mix_grad(self, B, W, nm, *args):
+        self._add(4 * nm * B * W * W, nm * (4 * B * W + 2 * W * W))
+        super().mix_grad(B, W, nm, *args)
+
+    def idft_yt(self, B, X, Y, T, m, W, *args):
+        n = B * X * Y * T
+        self._add(n * W * (W + 2 * m) + B * X * W * Y * 2 * m * 4 * m, W * (3 * n + B * X * 4 * m * m))
+        super().idft_yt(B, X, Y, T, m, W, *args)
 
 
 def bench_main(argv=None):
