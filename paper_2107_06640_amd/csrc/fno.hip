@@ -260,10 +260,28 @@ __global__ __launch_bounds__(256) void k_rel_l2(int64_t n, const float* yhat, co
   const float* yh = yhat + b * n;
   const float* yy = y + b * n;
   float se = 0.0f, sy = 0.0f;
-  for (int64_t j = threadIdx.x; j < n; j += 256) {
-    const float d = yh[j] - yy[j];
+  // one work-group per sample is bound by the latency of its loads: 16 of each
+  // array in flight per thread, added in order
+  constexpr int U = 16;
+  int64_t j0 = threadIdx.x;
+  for (; j0 + (U - 1) * 256 < n; j0 += U * 256) {
+    float h[U], t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      h[u] = yh[j0 + u * 256];
+      t[u] = yy[j0 + u * 256];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float d = h[u] - t[u];
+      se += d * d;
+      sy += t[u] * t[u];
+    }
+  }
+  for (; j0 < n; j0 += 256) {
+    const float d = yh[j0] - yy[j0];
     se += d * d;
-    sy += yy[j] * yy[j];
+    sy += yy[j0] * yy[j0];
   }
   r0[threadIdx.x] = se;
   r1[threadIdx.x] = sy;
@@ -279,7 +297,16 @@ __global__ __launch_bounds__(256) void k_rel_l2(int64_t n, const float* yhat, co
   if (threadIdx.x == 0) per[b] = ne / ny;
   if (grad) {
     const float s = (ne > 0.0f ? inv_batch / (ne * ny) : 0.0f);
-    for (int64_t j = threadIdx.x; j < n; j += 256) grad[b * n + j] = s * (yh[j] - yy[j]);
+    float* gb = grad + b * n;
+    int64_t j1 = threadIdx.x;
+    for (; j1 + (U - 1) * 256 < n; j1 += U * 256) {
+      float d[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) d[u] = yh[j1 + u * 256] - yy[j1 + u * 256];
+#pragma unroll
+      for (int u = 0; u < U; ++u) gb[j1 + u * 256] = s * d[u];
+    }
+    for (; j1 < n; j1 += 256) gb[j1] = s * (yh[j1] - yy[j1]);
   }
 }
 

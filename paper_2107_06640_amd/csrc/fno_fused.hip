@@ -29,6 +29,7 @@ namespace {
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f2 __attribute__((ext_vector_type(2)));
 typedef float f8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16;
@@ -85,13 +86,19 @@ __device__ __forceinline__ void store4(float* p, int64_t i, int64_t n, f4 x) {
 }
 
 // dst[r][k] = BF16 of src(r, k) = src[r * sr + k * sk], zero outside rows x cols, for a
-// prows x pcols image with leading dimension ld
-__device__ void stage(u16* dst, const float* src, int64_t sr, int64_t sk, int rows, int cols, int prows, int pcols,
-                      int ld, int tid, int nt) {
-  for (int i = tid; i < prows * pcols; i += nt) {
+// prows x pcols image (pcols a multiple of 8) with leading dimension ld. A thread moves eight
+// K entries at a time, so that their loads are in flight together; consecutive threads walk
+// the unit-stride index.
+__device__ __forceinline__ void stage(u16* dst, const float* src, int64_t sr, int64_t sk, int rows, int cols,
+                                      int prows, int pcols, int ld, int tid, int nt) {
+  const int k8s = pcols / 8;
+  for (int i = tid; i < prows * k8s; i += nt) {
     int r, k;
-    if (sk == 1) { r = i / pcols; k = i - r * pcols; } else { k = i / prows; r = i - k * prows; }
-    dst[r * ld + k] = (r < rows && k < cols) ? bits(src[r * sr + k * sk]) : (u16)0;
+    if (sk == 1) { r = i / k8s; k = 8 * (i - r * k8s); } else { k = i / prows; r = i - k * prows; k *= 8; }
+    f8 x;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = (r < rows && k + j < cols) ? src[r * sr + (k + j) * sk] : 0.0f;
+    *reinterpret_cast<bf8*>(dst + r * ld + k) = pack8(x);
   }
 }
 
@@ -232,7 +239,7 @@ __global__ __launch_bounds__(256) void k_head(int64_t n, int W, int H, const flo
 // dQ1, dq1, dQ2 summed over the points in registers and added to memory once
 // per work-group (cleared before).
 template <int KC, int HC, bool V4>
-__global__ __launch_bounds__(256) void k_head_bwd(int64_t n, int W, int H, const float* Q1, const float* q1,
+__global__ __launch_bounds__(256, KC * HC == 1 ? 2 : 1) void k_head_bwd(int64_t n, int W, int H, const float* Q1, const float* q1,
                                                   const float* Q2, const float* v, const float* dy, float* dv,
                                                   float* dQ1, float* dq1, float* dQ2) {
   constexpr int LD = 128 * HC + 8, LP = 64 + 8, WT = 2 * KC;
@@ -574,12 +581,26 @@ __global__ __launch_bounds__(256) void k_dft_x(XArgs a) {
     const int j0 = int(t - b * chunks) * kXCols;
     const float* in = a.in + b * a.K * P * a.inner + j0;
     __syncthreads();
-    // inner is even, so pairs of columns are aligned 8-byte loads
-    for (int i = tid; i < a.K * P * (kXCols / 2); i += 256) {
-      const int jj = 2 * (i % (kXCols / 2)), kp = i / (kXCols / 2), k = kp / P, p = kp - k * P;
-      const f2 x = j0 + jj < a.inner ? *reinterpret_cast<const f2*>(in + (int64_t)kp * a.inner + jj) : f2{0.f, 0.f};
-      sB[(p * kXCols + jj) * ld + k] = bits(x[0]);
-      sB[(p * kXCols + jj + 1) * ld + k] = bits(x[1]);
+    // a thread moves two K entries of two columns (inner is even: aligned 8-byte loads), four such
+    // blocks in flight
+    const int blocks = (a.K + 1) / 2 * P * (kXCols / 2);
+    for (int i0 = tid; i0 < blocks; i0 += 4 * 256) {
+      f2 x[4], y[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + 256 * u, jj = 2 * (i % (kXCols / 2)), kp = i / (kXCols / 2), p = kp % P, k = 2 * (kp / P);
+        const bool ok = i < blocks && j0 + jj < a.inner;
+        const float* q = in + (int64_t)(k * P + p) * a.inner + jj;
+        x[u] = ok ? *reinterpret_cast<const f2*>(q) : f2{0.f, 0.f};
+        y[u] = ok && k + 1 < a.K ? *reinterpret_cast<const f2*>(q + (int64_t)P * a.inner) : f2{0.f, 0.f};
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + 256 * u, jj = 2 * (i % (kXCols / 2)), kp = i / (kXCols / 2), p = kp % P, k = 2 * (kp / P);
+        if (i >= blocks) continue;
+        *reinterpret_cast<bf2*>(sB + (p * kXCols + jj) * ld + k) = __builtin_convertvector(f2{x[u][0], y[u][0]}, bf2);
+        *reinterpret_cast<bf2*>(sB + (p * kXCols + jj + 1) * ld + k) = __builtin_convertvector(f2{x[u][1], y[u][1]}, bf2);
+      }
     }
     __syncthreads();
     for (int i = w; i < RT * (kXCols / 16); i += 4) {
@@ -778,8 +799,9 @@ __global__ __launch_bounds__(64 * kMixWaves) void k_mix_grad(int B, int W, int64
 //   V[o][y][(p, kt)] = sum_k G_p[y][k] V2[o][k][kt],
 //   s[o][y][t] = sum V[o][y][(p, kt)] Bt((p, kt), t),
 //   z = s + Wm v (+ bias), a = gelu(z) or z.
-// First the wavefronts share out the channels and leave s in LDS, then they
-// share out the points, where the channel product is formed and s added. The
+// For 16 channels at a time the wavefronts first share out the channels and
+// leave s in LDS, then they share out the points, where the channel product is
+// formed from the fragments of v that each keeps in registers, and s added. The
 // activations are read and written once (the chain of products moved z five
 // times); bound by these.
 struct YtArgs {
@@ -795,26 +817,54 @@ struct YtArgs {
   int act;
 };
 
-template <int MT, bool V4>
+// bytes of LDS before s[o][point]: Wm and the wavefronts' V
+__host__ __device__ constexpr int yt_head(int MT) { return 2 * (16 * MT * (32 * ((MT + 1) / 2) + 8) + 4 * 16 * 40); }
+
+template <int MT, int NTL, bool V4>
 __global__ __launch_bounds__(256) void k_idft_yt(YtArgs q) {
   constexpr int KC = (MT + 1) / 2, LW = 32 * KC + 8, LV = 32 + 8;
+  constexpr bool LATE = NTL * KC <= 2;  // the loads of v stay in flight over the first transforms
   extern __shared__ __align__(16) unsigned char smem[];
   const int T = q.T, m = q.m, W = q.W, Y = q.Y, NTt = (T + 15) / 16;
-  const int lp = up(16 * T, 4) + 4;                              // points per channel in LDS, padded
+  const int lp = 16 * T + 4;                                     // points per channel in LDS, padded
   u16* sW = reinterpret_cast<u16*>(smem);                        // Wm[o][i]
   u16* sV = sW + 16 * MT * LW + (threadIdx.x >> 6) * 16 * LV;    // this wavefront's V[y][(p, kt)]
-  float* sS = reinterpret_cast<float*>(sW + 16 * MT * LW + 4 * 16 * LV);  // s[o][point]
+  float* sS = reinterpret_cast<float*>(smem + yt_head(MT));      // s[o][point] of 16 channels
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, c = lane & 15;
   const int ytiles = (Y + 15) / 16;
   const int64_t bx = blockIdx.x / ytiles;
   const int y0 = int(blockIdx.x - bx * ytiles) * 16, ny = min(16, Y - y0);
   const int64_t BX = q.B * q.X, S = BX * Y * T, pbase = (bx * Y + y0) * T;
   const int np = ny * T;
+  // this wavefront's points 64 (w + 4 i) + 4c.. of all input channels
+  f4 x[NTL][KC][8];
+  bf8 b[NTL][KC][4];
+#pragma unroll
+  for (int i = 0; i < NTL; ++i)
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int ci = 32 * kc + 8 * g + j;
+        x[i][kc][j] = ci < W ? load4<V4>(q.v + (int64_t)ci * S + pbase, 64 * (w + 4 * i) + 4 * c, np) : zero4();
+      }
+  auto convert = [&]() {
+#pragma unroll
+    for (int i = 0; i < NTL; ++i)
+#pragma unroll
+      for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const f4(&r)[8] = x[i][kc];
+          b[i][kc][u] = pack8(f8{r[0][u], r[1][u], r[2][u], r[3][u], r[4][u], r[5][u], r[6][u], r[7][u]});
+        }
+  };
+  if constexpr (!LATE) convert();
   stage(sW, q.Wm, q.sWo, q.sWi, W, W, 16 * MT, 32 * KC, LW, tid, 256);
   for (int i = lane; i < 16 * LV; i += 64) sV[i] = 0;
   // transform fragments: G_p rows y0.., K = 4m in up to two steps; Bt columns t
   const int GC = (4 * m + 31) / 32;
-  bf8 ag[2][2], bt[4];
+  bf8 ag[2][2], bt[NTL];
 #pragma unroll
   for (int kc = 0; kc < 2; ++kc) {
     f8 x0, x1;
@@ -829,90 +879,84 @@ __global__ __launch_bounds__(256) void k_idft_yt(YtArgs q) {
     ag[1][kc] = pack8(x1);
   }
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    f8 x;
+  for (int nt = 0; nt < NTL; ++nt) {
+    f8 y;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int k = 8 * g + j, t = 16 * nt + c;
-      x[j] = (k < 2 * m && t < T) ? q.Bt[k * q.sBk + t * q.sBn] : 0.0f;
+      y[j] = (k < 2 * m && t < T) ? q.Bt[k * q.sBk + t * q.sBn] : 0.0f;
     }
-    bt[nt] = pack8(x);
+    bt[nt] = pack8(y);
   }
   __syncthreads();
-  for (int o = w; o < W; o += 4) {
-    const float* V2 = q.V2 + ((int64_t)o * BX + bx) * 4 * m * m;
-    f4 a0 = zero4(), a1 = zero4();
 #pragma unroll
-    for (int kc = 0; kc < 2; ++kc) {
-      if (kc >= GC) continue;
-      f8 x;
+  for (int mt = 0; mt < MT; ++mt) {
+    // transforms of channels 16 mt + 4 w .. + 3, their spectra requested together
+    f8 sp[4][2];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int k = 32 * kc + 8 * g + j;
-        x[j] = (k < 4 * m && c < m) ? V2[k * m + c] : 0.0f;
+    for (int h = 0; h < 4; ++h)
+#pragma unroll
+      for (int kc = 0; kc < 2; ++kc) {
+        const int o = 16 * mt + 4 * w + h;
+        const float* V2 = q.V2 + ((int64_t)o * BX + bx) * 4 * m * m;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int k = 32 * kc + 8 * g + j;
+          sp[h][kc][j] = (o < W && k < 4 * m && c < m) ? V2[k * m + c] : 0.0f;
+        }
       }
-      const bf8 b = pack8(x);
-      a0 = mfma(ag[0][kc], b, a0);
-      a1 = mfma(ag[1][kc], b, a1);
-    }
-    if (c < m) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        sV[(4 * g + r) * LV + c] = bits(a0[r]);
-        sV[(4 * g + r) * LV + m + c] = bits(a1[r]);
+    for (int h = 0; h < 4; ++h) {
+      if (16 * mt + 4 * w + h >= W) continue;
+      f4 a0 = zero4(), a1 = zero4();
+#pragma unroll
+      for (int kc = 0; kc < 2; ++kc) {
+        if (kc >= GC) continue;
+        const bf8 f = pack8(sp[h][kc]);
+        a0 = mfma(ag[0][kc], f, a0);
+        a1 = mfma(ag[1][kc], f, a1);
       }
-    }
-    wave_sync();
-    const bf8 av = lds8(sV + c * LV + 8 * g);
-    float* s = sS + o * lp;
+      if (c < m) {
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      if (nt >= NTt) continue;
-      const f4 acc = mfma(av, bt[nt], zero4());
-      const int t = 16 * nt + c;
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (t < T) s[(4 * g + r) * T + t] = acc[r];
-    }
-    wave_sync();
-  }
-  __syncthreads();
-  const int tiles = (np + 63) / 64;
-  for (int t = w; t < tiles; t += 4) {
-    const int p = 64 * t + 4 * c;
-    f4 acc[MT][4];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) acc[mt][u] = zero4();
-#pragma unroll
-    for (int kc = 0; kc < KC; ++kc) {
-      f4 x[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int ci = 32 * kc + 8 * g + j;
-        x[j] = ci < W ? load4<V4>(q.v + (int64_t)ci * S + pbase, p, np) : zero4();
+        for (int r = 0; r < 4; ++r) {
+          sV[(4 * g + r) * LV + c] = bits(a0[r]);
+          sV[(4 * g + r) * LV + m + c] = bits(a1[r]);
+        }
       }
-      bf8 b[4];
+      wave_sync();
+      const bf8 av = lds8(sV + c * LV + 8 * g);
+      float* s = sS + (4 * w + h) * lp;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) b[u] = pack8(f8{x[0][u], x[1][u], x[2][u], x[3][u], x[4][u], x[5][u], x[6][u], x[7][u]});
+      for (int nt = 0; nt < NTL; ++nt) {
+        if (nt >= NTt) continue;
+        const f4 acc = mfma(av, bt[nt], zero4());
+        const int t = 16 * nt + c;
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
+        for (int r = 0; r < 4; ++r)
+          if (t < T) s[(4 * g + r) * T + t] = acc[r];
+      }
+      wave_sync();
+    }
+    if (LATE && mt == 0) convert();
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NTL; ++i) {
+      const int p = 64 * (w + 4 * i) + 4 * c;
+      f4 acc[4] = {zero4(), zero4(), zero4(), zero4()};
+#pragma unroll
+      for (int kc = 0; kc < KC; ++kc) {
         const bf8 a = lds8(sW + (16 * mt + c) * LW + 32 * kc + 8 * g);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) acc[mt][u] = mfma(a, b[u], acc[mt][u]);
+        for (int u = 0; u < 4; ++u) acc[u] = mfma(a, b[i][kc][u], acc[u]);
       }
-    }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int o = 16 * mt + 4 * g + r;
         if (o >= W || p >= np) continue;
-        const f4 s = *reinterpret_cast<const f4*>(sS + o * lp + p);
+        const f4 s = *reinterpret_cast<const f4*>(sS + (4 * g + r) * lp + p);
         f4 z;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) z[u] = s[u] + acc[mt][u][r];
+        for (int u = 0; u < 4; ++u) z[u] = s[u] + acc[u][r];
         if (q.bias) z += q.bias[o];
         const int64_t off = (int64_t)o * S + pbase;
         if (q.z) store4<V4>(q.z + off, p, np, z);
@@ -921,13 +965,12 @@ __global__ __launch_bounds__(256) void k_idft_yt(YtArgs q) {
           store4<V4>(q.a + off, p, np, z);
         }
       }
+    }
+    __syncthreads();
   }
 }
 
-int yt_lds(int W, int T) {
-  const int MT = (W + 15) / 16, KC = (MT + 1) / 2;
-  return 2 * (16 * MT * (32 * KC + 8) + 4 * 16 * 40) + 4 * W * (up(16 * T, 4) + 4);
-}
+int yt_lds(int W, int T) { return yt_head((W + 15) / 16) + 4 * 16 * (16 * T + 4); }
 int head_bwd_lds(int KC, int HC) {
   const int LD = 128 * HC + 8, LP = 72;
   return 2 * (64 * LD + 128 * HC * LP + 32 * KC * LP + 32 * KC * LD);
@@ -961,12 +1004,17 @@ int launch(unsigned grid, int threads, int lds, void* stream, A... args) {
   return done();
 }
 
-__global__ void k_clear(int64_t n, float* x) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    x[i] = 0.0f;
+// zeroes of up to three arrays
+__global__ void k_clear(int n0, float* x0, int n1, float* x1, int n2, float* x2) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n0) x0[i] = 0.0f;
+  if (i < n1) x1[i] = 0.0f;
+  if (i < n2) x2[i] = 0.0f;
 }
-int clear(int64_t n, float* x, void* stream) {
-  hipLaunchKernelGGL(k_clear, dim3(blocks((n + 255) / 256, 1)), dim3(256), 0, (hipStream_t)stream, n, x);
+int clear(int64_t n0, float* x0, int64_t n1, float* x1, int64_t n2, float* x2, void* stream) {
+  const int64_t n = std::max(n0, std::max(n1, n2));
+  hipLaunchKernelGGL(k_clear, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, (int)n0, x0, (int)n1,
+                     x1, (int)n2, x2);
   return done();
 }
 
@@ -1018,11 +1066,10 @@ int fno_head_backward(int64_t n, int64_t W, int64_t H, const float* Q1, const fl
                       const float* v, const float* dy, float* dv, float* dQ1, float* dq1, float* dQ2, void* stream) {
   if (n < 0 || W < 1 || H < 1 || W > kMaxW || H > kMaxH || !Q1 || !q1 || !Q2 || !v || !dy || !dv || !dQ1 || !dq1 || !dQ2)
     return -1;
-  int rc = clear(W * H, dQ1, stream);
-  if (rc == 0) rc = clear(H, dq1, stream);
-  if (rc == 0) rc = clear(H, dQ2, stream);
+  const int rc = clear(W * H, dQ1, H, dq1, H, dQ2, stream);
   if (rc || n == 0) return rc;
-  const unsigned grid = blocks((n + 63) / 64, 2);
+  // at least eight tiles per work-group, so that the sums it adds to memory do not outweigh its work
+  const unsigned grid = blocks((n + 511) / 512, 2);
   const bool a = vec4(n, v, dy);
 #define FNO_HEADB(KC, HC)                                                                                              \
   if ((W + 31) / 32 == KC && (H + 127) / 128 == HC)                                                                    \
@@ -1038,10 +1085,10 @@ int fno_head_backward(int64_t n, int64_t W, int64_t H, const float* Q1, const fl
 int fno_layer_backward(int64_t n, int64_t cout, int64_t cin, const float* z, const float* da, const float* x,
                        float* dz, float* dW, float* db, void* stream) {
   if (n < 0 || cout < 1 || cin < 1 || cout > kMaxW || cin > kMaxW || !da || !x || !dW || !db || (z && !dz)) return -1;
-  int rc = clear(cout * cin, dW, stream);
-  if (rc == 0) rc = clear(cout, db, stream);
+  const int rc = clear(cout * cin, dW, cout, db, 0, nullptr, stream);
   if (rc || n == 0) return rc;
-  const unsigned grid = blocks((n + 255) / 256, 2);
+  // at least four tiles per wavefront, as in fno_head_backward
+  const unsigned grid = blocks((n + 1023) / 1024, 2);
   const bool v = vec4(n, da, x) && (!z || vec4(n, z, dz));
   const int MT = int(cout + 15) / 16, NT = int(cin + 15) / 16;
 #define FNO_LB(M_, N_)                                                                                                \
@@ -1127,12 +1174,12 @@ int fno_idft_yt(int64_t B, int64_t X, int64_t Y, int64_t T, int64_t m, int64_t W
   const YtArgs q{B, X, (int)Y, (int)T, (int)m, (int)W, V2, G0, G1, Bt, sGm, sGk, sBk, sBn, Wm, v, sWo, sWi, bias, z, a, act};
   // rows of 16 T points, so every tile starts aligned where a (b, x) plane does
   const bool v4 = vec4(Y * T, v) && (!z || aligned16(z)) && (!a || aligned16(a));
-  switch ((W + 15) / 16) {
-#define FNO_YT(MT) \
-  case MT: return v4 ? launch<k_idft_yt<MT, true>>((unsigned)grid, 256, lds, stream, q) : launch<k_idft_yt<MT, false>>((unsigned)grid, 256, lds, stream, q);
-    FNO_YT(1) FNO_YT(2) FNO_YT(3)
+#define FNO_YT(MT, NTL)                                                                         \
+  if ((W + 15) / 16 == MT && (T + 15) / 16 <= NTL)                                              \
+    return v4 ? launch<k_idft_yt<MT, NTL, true>>((unsigned)grid, 256, lds, stream, q)           \
+              : launch<k_idft_yt<MT, NTL, false>>((unsigned)grid, 256, lds, stream, q);
+  FNO_YT(1, 1) FNO_YT(2, 1) FNO_YT(3, 1) FNO_YT(1, 2) FNO_YT(2, 2) FNO_YT(3, 2) FNO_YT(1, 4) FNO_YT(2, 4) FNO_YT(3, 4)
 #undef FNO_YT
-  }
   return -1;
 }
 
