@@ -135,6 +135,15 @@ hipError_t upload(Buffers& b, X** dst, const std::vector<Y>& src) {
 bool due_predict(int s, int c) { return (s % (1 << c)) == 0; }
 bool due_correct(int s, int c) { return ((s + 1) % (1 << c)) == 0; }
 
+// n matrices [rows][cols] as [cols][rows]
+std::vector<double> transposed(const std::vector<double>& a, int n, int rows, int cols) {
+  std::vector<double> r(a.size());
+  for (int i = 0; i < n; ++i)
+    for (int j = 0; j < rows; ++j)
+      for (int k = 0; k < cols; ++k) r[(size_t(i) * cols + k) * rows + j] = a[(size_t(i) * rows + j) * cols + k];
+  return r;
+}
+
 template <typename T>
 int build_dev(seis_t* h, DevData<T>& d) {
   Model& M = h->M;
@@ -169,7 +178,7 @@ int build_dev(seis_t* h, DevData<T>& d) {
 template <typename T>
 void share_common(const DevData<double>& c, DevData<T>& d) {
   d.tgt = c.tgt; d.mode = c.mode; d.hperm = c.hperm; d.half2 = c.half2; d.rhalf2 = c.rhalf2;
-  d.gslot = c.gslot; d.dslot = c.dslot; d.perm = c.perm; d.Eg = c.Eg; d.Lg = c.Lg; d.g_elem = c.g_elem; d.g_face = c.g_face;
+  d.gslot = c.gslot; d.dslot = c.dslot; d.perm = c.perm; d.Egt = c.Egt; d.Lgt = c.Lgt; d.g_elem = c.g_elem; d.g_face = c.g_face;
   d.g_par = c.g_par; d.eta = c.eta;
 }
 
@@ -178,7 +187,7 @@ int build_common(seis_t* h, DevData<double>& c) {
   Buffers& b = h->buf;
   int32_t *tgt, *half2, *rhalf2, *gslot, *dslot, *perm, *gelem;
   int8_t *mode, *hperm, *gface;
-  double *Eg, *Lg, *gpar, *eta;
+  double *Egt, *Lgt, *gpar, *eta;
   HIPCHK(h, upload(b, &tgt, M.tgt), "upload tgt");
   HIPCHK(h, upload(b, &mode, M.mode), "upload mode");
   HIPCHK(h, upload(b, &hperm, M.hperm), "upload hperm");
@@ -187,8 +196,8 @@ int build_common(seis_t* h, DevData<double>& c) {
   HIPCHK(h, upload(b, &gslot, M.gslot), "upload gslot");
   HIPCHK(h, upload(b, &dslot, M.dslot), "upload dslot");
   HIPCHK(h, upload(b, &perm, M.ref.perm), "upload perm");
-  HIPCHK(h, upload(b, &Eg, M.ref.Eg), "upload Eg");
-  HIPCHK(h, upload(b, &Lg, M.ref.Lg), "upload Lg");
+  HIPCHK(h, upload(b, &Egt, transposed(M.ref.Eg, 4, M.nq, M.B)), "upload Eg");
+  HIPCHK(h, upload(b, &Lgt, transposed(M.ref.Lg, 4, M.B, M.nq)), "upload Lg");
   std::vector<int32_t> ge(M.g_elem.begin(), M.g_elem.end());
   HIPCHK(h, upload(b, &gelem, ge), "upload g_elem");
   HIPCHK(h, upload(b, &gface, M.g_face), "upload g_face");
@@ -269,7 +278,7 @@ int build_common(seis_t* h, DevData<double>& c) {
   }
   c.tgt = tgt; c.mode = mode; c.hperm = hperm; c.half2 = half2; c.rhalf2 = rhalf2; c.gslot = gslot;
   c.dslot = dslot;
-  c.perm = perm; c.Eg = Eg; c.Lg = Lg; c.g_elem = gelem; c.g_face = gface; c.g_par = gpar; c.eta = eta;
+  c.perm = perm; c.Egt = Egt; c.Lgt = Lgt; c.g_elem = gelem; c.g_face = gface; c.g_par = gpar; c.eta = eta;
   c.g = M.g;
   return SEIS_OK;
 }

@@ -60,8 +60,8 @@ struct DevData {
   const T* Lf;  // [4][B][Bf]
   const int32_t* perm;  // [6][Bf]
   // gravity (FP64)
-  const double* Eg;     // [4][nq][B]
-  const double* Lg;     // [4][B][nq]
+  const double* Egt;    // [4][B][nq] traces at the eta points of a face, point-contiguous
+  const double* Lgt;    // [4][nq][B] their lifts, row-contiguous
   const int32_t* g_elem;
   const int8_t* g_face;
   const double* g_par;  // [F_g][8]

@@ -192,7 +192,10 @@ __global__ __launch_bounds__(NT_TALL) void k_correct_plain(DevData<T> d, int64_t
 // predicted solution (p = -n.s.n), the ODE d eta/dt = f - a eta, dH/dt = eta
 // integrated exactly through its Taylor series over the element's step, and
 // the time-integrated boundary flux (stress rows -lambda (eta1 - eta0),
-// velocity rows g H n) lifted with the face rule.
+// velocity rows g H n) lifted with the face rule. Bound by latency (traces,
+// the series, lifts, each behind a barrier): 1152 faces at order 6 took 50 us with
+// row-contiguous matrices, the zero rows of the derivatives and two FP64 divisions per
+// term, 42 us in this form.
 template <typename T, int N>
 __global__ __launch_bounds__(256) void k_gravity(DevData<T> d, const int32_t* glist) {
   constexpr int B = nbasis(N);
@@ -205,60 +208,73 @@ __global__ __launch_bounds__(256) void k_gravity(DevData<T> d, const int32_t* gl
   const double* par = d.g_par + gf * 8;
   const double scale = par[0], nx = par[1], ny = par[2], nz = par[3], Z = par[4], a = par[5], lam = par[6],
                dt = par[7];
+  constexpr int terms = N + 24;  // of the Taylor series
   __shared__ T sD[(N + 1) * B * 9];
-  __shared__ double sFm[nq][N + 1];
-  __shared__ double sF[nq][2];
-  // the element's scaled time derivatives, staged once (coalesced)
+  __shared__ double sFm[N + 1][nq], sF[2][nq], sStep[terms], sInv[terms];
+  // the element's scaled time derivatives, staged once (coalesced): the rows of derivative k below B_{N-k}
   const T* D = d.gD + (int64_t)gf * (N + 1) * B * 9;
-  for (int i = tid; i < (N + 1) * B * 9; i += 256) sD[i] = D[i];
-  __syncthreads();
-  // trace of each derivative at each surface point: one (point, order) pair per thread
-  for (int w = tid; w < nq * (N + 1); w += 256) {
-    const int q = w / (N + 1), m = w % (N + 1);
-    const double* Eq = d.Eg + ((size_t)face * nq + q) * B;
-    double v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll 8
-    for (int l = 0; l < B; ++l) {
-      const double el = Eq[l];
 #pragma unroll
-      for (int p = 0; p < 9; ++p) v[p] += el * (double)sD[(m * B + l) * 9 + p];
+  for (int k = 0; k <= N; ++k)
+    for (int i = tid; i < nbasis(N - k) * 9; i += 256) sD[k * B * 9 + i] = D[k * B * 9 + i];
+  // the series' coefficients, once per work-group: the divisions of a point's
+  // recurrence would be a chain of their own
+  if (tid < terms) {
+    sStep[tid] = dt / (tid + 1);
+    sInv[tid] = 1.0 / (tid + 2);
+  }
+  __syncthreads();
+  // trace of each derivative at each surface point: one (order, point) pair per
+  // thread, so that a wavefront has few lengths of sum and reads the matrix coalesced
+  for (int w = tid; w < nq * (N + 1); w += 256) {
+    const int m = w / nq, q = w - m * nq;
+    const double* Eq = d.Egt + (size_t)face * B * nq + q;
+    const T* Dm = sD + m * B * 9;
+    double v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    const int rows = nbasis(N - m);
+#pragma unroll 4
+    for (int l = 0; l < rows; ++l) {
+      const double el = Eq[l * nq];
+#pragma unroll
+      for (int p = 0; p < 9; ++p) v[p] += el * (double)Dm[l * 9 + p];
     }
     const double tx = v[0] * nx + v[3] * ny + v[5] * nz;
     const double ty = v[3] * nx + v[1] * ny + v[4] * nz;
     const double tz = v[5] * nx + v[4] * ny + v[2] * nz;
     const double pm = -(tx * nx + ty * ny + tz * nz);
-    sFm[q][m] = v[6] * nx + v[7] * ny + v[8] * nz + pm / Z;
+    sFm[m][q] = v[6] * nx + v[7] * ny + v[8] * nz + pm / Z;
   }
   __syncthreads();
   for (int q = tid; q < nq; q += 256) {
     const double eta0 = d.eta[(int64_t)gf * nq + q];
     double em = eta0, eta1 = eta0, H = eta0 * dt;
-    for (int m = 0; m < N + 24; ++m) {
-      const double fm = m <= N ? sFm[q][m] : 0.0;
-      em = dt / (m + 1) * (fm - a * em);
+    for (int m = 0; m < terms; ++m) {
+      const double fm = m <= N ? sFm[m][q] : 0.0;
+      em = sStep[m] * (fm - a * em);
       eta1 += em;
-      H += em * dt / (m + 2);
+      // em dt / (m + 2), correctly rounded: the quotient by the reciprocal, corrected by its remainder
+      const double x = em * dt, r = sInv[m], y = x * r;
+      H += isfinite(y) ? fma(fma(-y, double(m + 2), x), r, y) : y;
     }
     d.eta[(int64_t)gf * nq + q] = eta1;
-    sF[q][0] = -lam * (eta1 - eta0);
-    sF[q][1] = d.g * H;
+    sF[0][q] = -lam * (eta1 - eta0);
+    sF[1][q] = d.g * H;
   }
   __syncthreads();
-  // lift: rows of the three normal stresses (p < 3) and the velocities (p >= 6)
-  const double nrm[3] = {nx, ny, nz};
-  for (int i = tid; i < B * 6; i += 256) {
-    const int kk = i / 6, j = i % 6;
-    const int p = j < 3 ? j : j + 3;
-    const double* Lq = d.Lg + ((size_t)face * B + kk) * nq;
+  // lift: rows of the three normal stresses (one sum) and the velocities
+  for (int i = tid; i < B * 4; i += 256) {
+    const int j = i / B, kk = i - j * B;
+    const double* Lq = d.Lgt + (size_t)face * nq * B + kk;
     double acc = 0.0;
-    if (p < 3) {
+    if (j == 0) {
 #pragma unroll 8
-      for (int q = 0; q < nq; ++q) acc += Lq[q] * sF[q][0];
+      for (int q = 0; q < nq; ++q) acc += Lq[q * B] * sF[0][q];
+      for (int p = 0; p < 3; ++p) d.Q[qidx(e, kk, p, RT)] -= (T)(scale * acc);
     } else {
+      const double nj = j == 1 ? nx : (j == 2 ? ny : nz);
 #pragma unroll 8
-      for (int q = 0; q < nq; ++q) acc += Lq[q] * sF[q][1] * nrm[p - 6];
+      for (int q = 0; q < nq; ++q) acc += Lq[q * B] * sF[1][q] * nj;
+      d.Q[qidx(e, kk, 5 + j, RT)] -= (T)(scale * acc);
     }
-    d.Q[qidx(e, kk, p, RT)] -= (T)(scale * acc);
   }
 }
 
