@@ -144,6 +144,18 @@ std::vector<double> transposed(const std::vector<double>& a, int n, int rows, in
   return r;
 }
 
+// whether the handle runs kernels with pointwise flux coefficients (every tuned one), and
+// whether it runs plain ones, with rotated flux matrices (chosen, an order
+// the group kernels lack, or a small range in 32 bits)
+template <typename T>
+bool pointwise_form(const seis_t* h) {
+  return h->kernel == SEIS_KERNEL_TUNED && group_order<T>(h->M.N);
+}
+template <typename T>
+bool plain_form(const seis_t* h) {
+  return !pointwise_form<T>(h) || h->precision != SEIS_FP64;
+}
+
 template <typename T>
 int build_dev(seis_t* h, DevData<T>& d) {
   Model& M = h->M;
@@ -159,8 +171,9 @@ int build_dev(seis_t* h, DevData<T>& d) {
   // operators: filled on the device by the assembly kernel
   HIPCHK(h, b.alloc(&G, E * 9), "alloc G");
   HIPCHK(h, b.alloc(&mat, E * 3), "alloc mat");
-  HIPCHK(h, b.alloc(&Fm, E * 4 * 81), "alloc Fm");
-  HIPCHK(h, b.alloc(&Fp, E * 4 * 81), "alloc Fp");
+  const int64_t nF = plain_form<T>(h) ? E * 4 * 81 : 0;
+  HIPCHK(h, b.alloc(&Fm, nF), "alloc Fm");
+  HIPCHK(h, b.alloc(&Fp, nF), "alloc Fp");
   HIPCHK(h, b.alloc(&In, in_size(E, FT)), "alloc In");
   HIPCHK(h, hipMemset(In, 0, in_size(E, FT) * sizeof(T)), "memset In");
   HIPCHK(h, b.alloc(&H2, std::max<int64_t>(M.n_half2, 1) * Bf * 9), "alloc H2");
@@ -305,20 +318,17 @@ int assemble_ops(seis_t* h) {
   if (st == hipSuccess) st = upload(tmp, &nbk, M.a_nbk);
   if (st != hipSuccess) return bail(st, "upload assembly inputs");
   const AsmInput in{M.E, Ji, ad, dt, lmr, nrm, area, kind, nbk};
-  const bool tuned = h->kernel == SEIS_KERNEL_TUNED && h->precision != SEIS_FP64;
-  float* rcm = tuned ? const_cast<float*>(h->tuned.a.RCm) : nullptr;
-  float* rcp = tuned ? const_cast<float*>(h->tuned.a.RCp) : nullptr;
-  if (h->precision == SEIS_FP64) {
-    DevData<double>& d = h->d64;
-    const AsmOutput<double> out{const_cast<double*>(d.G), const_cast<double*>(d.mat), const_cast<double*>(d.Fm),
-                                const_cast<double*>(d.Fp), nullptr, nullptr};
-    st = launch_assemble(in, out, nullptr);
-  } else {
-    DevData<float>& d = h->d32;
-    const AsmOutput<float> out{const_cast<float*>(d.G), const_cast<float*>(d.mat), const_cast<float*>(d.Fm),
-                               const_cast<float*>(d.Fp), rcm, rcp};
-    st = launch_assemble(in, out, nullptr);
-  }
+  // the operators of the forms that run
+  auto assemble = [&](auto& d, const auto* rcm, const auto* rcp) {
+    using T = std::remove_reference_t<decltype(*d.Q)>;
+    const bool plain = plain_form<T>(h), pointwise = pointwise_form<T>(h);
+    const AsmOutput<T> out{const_cast<T*>(d.G), const_cast<T*>(d.mat), plain ? const_cast<T*>(d.Fm) : nullptr,
+                           plain ? const_cast<T*>(d.Fp) : nullptr, pointwise ? const_cast<T*>(rcm) : nullptr,
+                           pointwise ? const_cast<T*>(rcp) : nullptr};
+    return launch_assemble(in, out, nullptr);
+  };
+  st = h->precision == SEIS_FP64 ? assemble(h->d64, h->tuned.g64.RCm, h->tuned.g64.RCp)
+                                 : assemble(h->d32, h->tuned.a.RCm, h->tuned.a.RCp);
   if (st == hipSuccess) st = hipDeviceSynchronize();
   if (st != hipSuccess) return bail(st, "operator assembly");
   tmp.release();

@@ -90,14 +90,14 @@ __global__ __launch_bounds__(64) void k_assemble(AsmInput in, AsmOutput<T> out) 
   if (out.RCm) {
     double cm[8], cp[8];
     pointwise_coeffs(kind, zpm, zsm, zpp, zsp, scale, cm, cp);
-    float* rm = out.RCm + id * 12;
-    float* rp = out.RCp + id * 12;
-    for (int d = 0; d < 3; ++d) rm[d] = rp[d] = (float)n[d];
+    T* rm = out.RCm + id * 12;
+    T* rp = out.RCp + id * 12;
+    for (int d = 0; d < 3; ++d) rm[d] = rp[d] = (T)n[d];
     for (int i = 0; i < 8; ++i) {
-      rm[3 + i] = (float)cm[i];
-      rp[3 + i] = (float)cp[i];
+      rm[3 + i] = (T)cm[i];
+      rp[3 + i] = (T)cp[i];
     }
-    rm[11] = rp[11] = 0.0f;
+    rm[11] = rp[11] = (T)0;
   }
 }
 

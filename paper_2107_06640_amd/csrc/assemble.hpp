@@ -30,8 +30,8 @@ struct AsmOutput {
   T* mat;      // [E][3]    lambda, mu, 1/rho
   T* Fm;       // [E][4][81] 2 A dt/|J| * T A- G- T^-1 (own trace), nullable
   T* Fp;       // [E][4][81] 2 A dt/|J| * T A- G+ T^-1 (neighbour trace), nullable
-  float* RCm;  // [E][4][12] pointwise middle-state coefficients, own trace, nullable
-  float* RCp;  // [E][4][12] pointwise middle-state coefficients, neighbour trace, nullable
+  T* RCm;      // [E][4][12] pointwise middle-state coefficients, own trace, nullable
+  T* RCp;      // [E][4][12] pointwise middle-state coefficients, neighbour trace, nullable
 };
 
 template <typename T>

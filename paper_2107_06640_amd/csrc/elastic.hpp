@@ -46,6 +46,37 @@ __device__ __forceinline__ T grad_op(int p, T lam, T mu, T rinv, const T* wx, co
   }
 }
 
+// Minus the Godunov flux A-hat^-(n) q^b at one face node (Sec. 4.2), with the
+// middle state a linear map of the given trace: c = n_x, n_y, n_z, then the
+// eight scaled coefficients of (s_n^b, v_n^b) from (s_n, v_n) and
+// (t_t^b, v_t^b) from (t_t, v_t).
+template <typename T>
+__device__ __forceinline__ void node_flux(const T* c, T lam, T mu, T rinv, const T* in, T* out) {
+  const T nx = c[0], ny = c[1], nz = c[2];
+  const T tx = in[0] * nx + in[3] * ny + in[5] * nz;
+  const T ty = in[3] * nx + in[1] * ny + in[4] * nz;
+  const T tz = in[5] * nx + in[4] * ny + in[2] * nz;
+  const T sn = tx * nx + ty * ny + tz * nz;
+  const T ttx = tx - sn * nx, tty = ty - sn * ny, ttz = tz - sn * nz;
+  const T vn = in[6] * nx + in[7] * ny + in[8] * nz;
+  const T vtx = in[6] - vn * nx, vty = in[7] - vn * ny, vtz = in[8] - vn * nz;
+  const T snb = c[3] * sn + c[4] * vn;
+  const T vnb = c[5] * sn + c[6] * vn;
+  const T tbx = c[7] * ttx + c[8] * vtx, tby = c[7] * tty + c[8] * vty, tbz = c[7] * ttz + c[8] * vtz;
+  const T vbx = c[9] * ttx + c[10] * vtx, vby = c[9] * tty + c[10] * vty, vbz = c[9] * ttz + c[10] * vtz;
+  const T w = T(2) * vnb;
+  // out is minus the flux (the sign every caller applies), so no sign flips
+  out[0] = lam * vnb + mu * (w * nx * nx + T(2) * vbx * nx);
+  out[1] = lam * vnb + mu * (w * ny * ny + T(2) * vby * ny);
+  out[2] = lam * vnb + mu * (w * nz * nz + T(2) * vbz * nz);
+  out[3] = mu * (w * nx * ny + vbx * ny + vby * nx);
+  out[4] = mu * (w * ny * nz + vby * nz + vbz * ny);
+  out[5] = mu * (w * nx * nz + vbx * nz + vbz * nx);
+  out[6] = rinv * (snb * nx + tbx);
+  out[7] = rinv * (snb * ny + tby);
+  out[8] = rinv * (snb * nz + tbz);
+}
+
 __host__ __device__ constexpr int nbasis(int N) { return (N + 1) * (N + 2) * (N + 3) / 6; }
 __host__ __device__ constexpr int nface(int N) { return (N + 1) * (N + 2) / 2; }
 

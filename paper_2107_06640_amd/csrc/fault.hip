@@ -72,6 +72,7 @@ __global__ __launch_bounds__(kFaultThreads) void k_fault(FaultArgs a, const T* g
   const T* Dm = gD + (int64_t)a.dslot[em] * ND;
   const T* Dp = gD + (int64_t)a.dslot[ep] * ND;
   for (int i = threadIdx.x; i < ND; i += blockDim.x) {
+    if (i % (B * 9) >= nbasis(N - i / (B * 9)) * 9) continue;  // derivative k has B_{N-k} rows, the rest is zero
     sd[0][i] = Dm[i];
     sd[1][i] = Dp[i];
   }
@@ -83,8 +84,9 @@ __global__ __launch_bounds__(kFaultThreads) void k_fault(FaultArgs a, const T* g
     const double* Em = a.E + ((int64_t)(side == 0 ? fm : fp) * Bf + node) * B;
     const T* D = &sd[side][k * B * 9 + p];
     double acc = 0.0;
+    const int rows = nbasis(N - k);
 #pragma unroll 8
-    for (int l = 0; l < B; ++l) acc += Em[l] * (double)D[l * 9];
+    for (int l = 0; l < rows; ++l) acc += Em[l] * (double)D[l * 9];
     tr[side][k][m][p] = acc;
   }
   __syncthreads();

@@ -79,10 +79,8 @@ __global__ __launch_bounds__(NT_TALL) void k_predict_plain(DevData<T> d, int64_t
       sD[i] = v;
       sI[i] += v / T(k + 2);
       sIh[i] += v * half / T(k + 2);
-      if (gD) gD[(k + 1) * B * 9 + i] = v;
+      if (gD) gD[(k + 1) * B * 9 + i] = v;  // rows below B_{N-k-1}: the others are not read
     }
-    if (gD)
-      for (int i = nout * 9 + tid; i < B * 9; i += NT) gD[(k + 1) * B * 9 + i] = T(0);
     half *= T(0.5);
     __syncthreads();
   }

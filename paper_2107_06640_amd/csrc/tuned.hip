@@ -173,6 +173,101 @@ hipError_t corr_dispatch_any(int precision, int N, const LaunchCfg& c, const TAr
   return corr_dispatch_bf16(N, c, a, e0, e1, s);
 }
 
+// Half-step hand-over: the groups with a face towards a finer neighbour (slot in
+// Ih) and, per cluster, their runs of the model's fix_list (sorted by element).
+struct FinerLists {
+  std::vector<int32_t> hslot, runs;
+  std::vector<int64_t> start;
+  int32_t slots = 0;
+};
+
+FinerLists finer_lists(const Model& M) {
+  FinerLists r;
+  r.hslot.assign((M.E + 15) / 16, -1);
+  r.start.assign(M.C + 1, 0);
+  for (int c = 0; c < M.C; ++c) {
+    r.start[c] = (int64_t)r.runs.size() / 3;
+    int32_t last = -1;
+    for (int64_t i = M.fix_start[c]; i < M.fix_start[c + 1]; ++i) {
+      const int32_t grp = M.fix_list[i] >> 6;  // entries are element * 4 + face
+      if (r.hslot[grp] < 0) r.hslot[grp] = r.slots++;
+      if (grp != last) {
+        r.runs.insert(r.runs.end(), {grp, int32_t(i), 0});
+        last = grp;
+      }
+      ++r.runs.back();
+    }
+  }
+  r.start[M.C] = (int64_t)r.runs.size() / 3;
+  return r;
+}
+
+template <typename T>
+hipError_t alloc(std::vector<void*>& owned, int64_t& bytes, T** dst, int64_t n) {
+  void* p = nullptr;
+  const int64_t b = std::max<int64_t>(n, 1) * (int64_t)sizeof(T);
+  const hipError_t st = hipMalloc(&p, b);
+  if (st != hipSuccess) return st;
+  owned.push_back(p);
+  bytes += b;
+  *dst = static_cast<T*>(p);
+  return hipSuccess;
+}
+
+// Arguments of the group kernels (the pointwise flux coefficients are filled by the assembly).
+template <typename T>
+hipError_t group_build(GroupArgs<T>& a, TunedData& t, const Model& M, const DevData<T>& d, std::vector<void*>& owned,
+                       int64_t& bytes) {
+  a.Q = d.Q;
+  a.In = d.In;
+  a.G = d.G;
+  a.mat = d.mat;
+  a.H2 = d.H2;
+  a.gD = d.gD;
+  a.tgt = d.tgt;
+  a.half2 = d.half2;
+  a.rhalf2 = d.rhalf2;
+  const FinerLists fl = finer_lists(M);
+  t.run_start = fl.start;
+  // a group hands over from its slot of I~_h: derivatives only for gravity and fault faces
+  std::vector<int32_t> mh(M.E, 0), ds(M.gslot.begin(), M.gslot.end());
+  for (size_t k = 0; k < M.f_elem.size(); ++k)
+    for (int64_t e : {int64_t(M.f_elem[k]), int64_t(M.f_pelem[k])}) ds[e] = M.dslot[e];
+  for (int64_t e = 0; e < M.E; ++e)
+    for (int f = 0; f < 4; ++f) mh[e] |= ((M.mode[e * 4 + f] & 3) | (M.hperm[e * 4 + f] & 7) << 2) << (8 * f);
+  const int B = n_basis(M.N), Bf = (M.N + 1) * (M.N + 2) / 2;
+  std::vector<double> Et(size_t(4) * B * Bf);
+  for (int f = 0; f < 4; ++f)
+    for (int m = 0; m < Bf; ++m)
+      for (int l = 0; l < B; ++l) Et[(size_t(f) * B + l) * Bf + m] = M.ref.E[(size_t(f) * Bf + m) * B + l];
+  T *rcm, *rcp, *ih, *img, *et;
+  int32_t *pinv, *dm, *dl, *hs, *fx, *runs;
+  hipError_t st = alloc(owned, bytes, &rcm, M.E * 48);
+  if (st == hipSuccess) st = alloc(owned, bytes, &rcp, M.E * 48);
+  if (st == hipSuccess) st = alloc(owned, bytes, &ih, fl.slots * int64_t(row_tiles(B) * 36 * 64));
+  if (st == hipSuccess) st = upload(owned, bytes, &img, group_image(M, sizeof(T) == 8));
+  if (st == hipSuccess) st = upload(owned, bytes, &et, Et);
+  if (st == hipSuccess) st = upload(owned, bytes, &pinv, M.ref.pinv);
+  if (st == hipSuccess) st = upload(owned, bytes, &dm, mh);
+  if (st == hipSuccess) st = upload(owned, bytes, &dl, ds);
+  if (st == hipSuccess) st = upload(owned, bytes, &hs, fl.hslot);
+  if (st == hipSuccess) st = upload(owned, bytes, &fx, M.fix_list);
+  if (st == hipSuccess) st = upload(owned, bytes, &runs, fl.runs);
+  if (st != hipSuccess) return st;
+  a.RCm = rcm;
+  a.RCp = rcp;
+  a.Ih = ih;
+  a.Et = et;
+  a.img = img;
+  a.pinv = pinv;
+  a.mh4 = dm;
+  a.dslot = dl;
+  a.hslot = hs;
+  a.fix_list = fx;
+  a.fix_group = runs;
+  return hipSuccess;
+}
+
 hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevData<double>& d64,
                        const DevData<float>& d32, int tile, int acoustic, std::vector<void*>& owned,
                        int64_t& bytes) {
@@ -188,10 +283,15 @@ hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevDat
     t.cc = LaunchCfg{w, 0, 0, 2};
     t.fixed = 1;
   }
-  if (precision == 0) {  // FP64 runs the plain kernels
-    t.ready = 1;
-    return hipSuccess;
+  t.run_start.assign(M.C + 1, 0);
+  if (precision == 0) {
+    const hipError_t sg = group_order<double>(M.N) ? group_build(t.g64, t, M, d64, owned, bytes) : hipSuccess;
+    t.ready = sg == hipSuccess;
+    return sg;
   }
+  hipError_t st = hipSuccess;
+  if (precision == 1) st = group_build(t.g32, t, M, d32, owned, bytes);
+  if (st != hipSuccess) return st;
   TArgs& a = t.a;
   a.Q = d32.Q;
   a.In = d32.In;
@@ -214,9 +314,9 @@ hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevDat
     bytes += nJ * int64_t(sizeof(float));
     a.Ib = static_cast<float*>(pj);
   }
-  // pointwise flux coefficients: filled by the operator assembly
-  float* rc[2] = {nullptr, nullptr};
-  for (int i = 0; i < 2; ++i) {
+  // pointwise flux coefficients: filled by the operator assembly (shared with the group kernels)
+  float* rc[2] = {const_cast<float*>(t.g32.RCm), const_cast<float*>(t.g32.RCp)};
+  for (int i = 0; i < 2 && !rc[i]; ++i) {
     void* p = nullptr;
     const int64_t n = M.E * 4 * 12;
     hipError_t sa = hipMalloc(&p, n * sizeof(float));
@@ -227,7 +327,7 @@ hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevDat
   }
   float *rcm = rc[0], *rcp = rc[1];
   int32_t* pinv;
-  hipError_t st = upload(owned, bytes, &pinv, M.ref.pinv);
+  st = upload(owned, bytes, &pinv, M.ref.pinv);
   if (st != hipSuccess) return st;
   a.RCm = rcm;
   a.RCp = rcp;
@@ -303,9 +403,34 @@ hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevDat
   return hipSuccess;
 }
 
+namespace {
+
+// FP32 ranges that run on the group kernels: too few elements to fill the chip
+// with a wavefront per 16 (mc_min), but enough groups to keep more of it busy
+// than the plain kernels' work-group per element. At order 6, predictor: 106 elements 26 us
+// plain and 46 us grouped (7 work-groups), 1971 elements 122 us and 50 us; 1296 at order 3
+// 12 us and 11 us. Small ranges of the BF16 precisions stay on the plain
+// kernels: BF16 rounding amplifies another order of the FP32 sums (one ulp in a few
+// elements of a small cluster becomes 3e-4 of the result in four steps).
+constexpr int64_t kGroupMin = 256;
+bool group_range(const TunedData& t, int precision, int64_t n) {
+  return precision == 1 && n >= kGroupMin && n < t.mc_min;
+}
+
+}  // namespace
+
 hipError_t tuned_predict(const TunedData& t, int precision, int N, int c0, int c1, int64_t e0, int64_t e1,
                          const Sched& sc, hipStream_t s) {
-  if (precision == 0) return launch_predict_plain<double>(N, t.d64, e0, e1 - e0, sc, s);
+  const int64_t r0 = t.run_start[c0], nr = t.run_start[c1 + 1] - r0;
+  if (precision == 0) {
+    if (!group_order<double>(N)) return launch_predict_plain<double>(N, t.d64, e0, e1 - e0, sc, s);
+    const hipError_t st = launch_predict_group<double>(N, t.g64, e0, e1, sc, s);
+    return st == hipSuccess ? launch_finer<double>(N, t.g64, r0, nr, s) : st;
+  }
+  if (group_range(t, precision, e1 - e0)) {
+    const hipError_t st = launch_predict_group<float>(N, t.g32, e0, e1, sc, s);
+    return st == hipSuccess ? launch_finer<float>(N, t.g32, r0, nr, s) : st;
+  }
   if (e1 - e0 < t.mc_min) return launch_predict_plain<float>(N, t.d32, e0, e1 - e0, sc, s);
   hipError_t st = pred_dispatch_any(precision, N, t.pc, t.a, e0, e1, sc, s);
   if (st != hipSuccess) return st;
@@ -315,7 +440,10 @@ hipError_t tuned_predict(const TunedData& t, int precision, int N, int c0, int c
 
 hipError_t tuned_correct(const TunedData& t, int precision, int N, int c0, int c1, int64_t e0, int64_t e1,
                          const Sched& sc, hipStream_t s) {
-  if (precision == 0) return launch_correct_plain<double>(N, t.d64, e0, e1 - e0, sc, s);
+  if (precision == 0)
+    return group_order<double>(N) ? launch_correct_group<double>(N, t.g64, e0, e1, sc, s)
+                                  : launch_correct_plain<double>(N, t.d64, e0, e1 - e0, sc, s);
+  if (group_range(t, precision, e1 - e0)) return launch_correct_group<float>(N, t.g32, e0, e1, sc, s);
   if (e1 - e0 < t.mc_min) return launch_correct_plain<float>(N, t.d32, e0, e1 - e0, sc, s);
   // second-half traces into the inbox of the clusters on the second step of
   // their pair (h2_list is ordered by cluster): one launch per run of such

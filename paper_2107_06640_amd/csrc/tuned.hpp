@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "device.hpp"
+#include "group.hpp"
 #include "model.hpp"
 
 namespace seis {
@@ -55,10 +56,13 @@ struct TunedData {
   LaunchCfg pc{}, cc{};  // predictor, corrector
   int fixed = 0;         // configuration fixed by the caller (options.tile)
   int source = 0;        // 0 default or fixed, 1 measured at set-up, 2 read from the tuning cache
-  int64_t mc_min = 0;    // clusters with fewer elements run on the plain FP32 kernels
+  int64_t mc_min = 0;    // ranges of fewer elements run on the FP32 group or plain kernels
   int64_t n_acoustic_groups = 0;  // 16-element groups run in the 4-quantity form
   TArgs a{};
   std::vector<int64_t> fix_start, h2_start;  // per cluster: ranges of fix_list and h2_list
+  std::vector<int64_t> run_start;            // per cluster: ranges of the group arguments' fix_group
+  GroupArgs<double> g64{};   // FP64
+  GroupArgs<float> g32{};    // FP32 ranges below mc_min
   DevData<double> d64{};
   DevData<float> d32{};
 };
@@ -80,13 +84,13 @@ hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevDat
                        const DevData<float>& d32, int tile, int acoustic, std::vector<void*>& owned,
                        int64_t& bytes);
 // Clusters c0..c1 = elements [e0, e1) (a launch may span several clusters;
-// sc gives each element's step parity). FP64 runs the plain kernels, and so
-// does a range of fewer than mc_min elements (in FP32). Otherwise the
-// matrix-core predictor handles every element; faces handing over to a finer
-// neighbour are then rewritten with the first- and second-half traces, and
-// before the corrector the second-half traces of the clusters on the second
-// step of their pair are copied into the inbox of the finer elements that
-// read them.
+// sc gives each element's step parity). FP64 runs the group kernels (orders
+// 3..6, else the plain ones). A range of fewer than mc_min elements runs in FP32 on the
+// group or the plain kernels, a larger one on the matrix-core kernels, after which
+// faces handing over to a finer neighbour are rewritten with the first- and
+// second-half traces; before the matrix-core corrector the second-half traces
+// of the clusters on the second step of their pair are copied into the inbox of
+// the finer elements that read them.
 hipError_t tuned_predict(const TunedData& t, int precision, int N, int c0, int c1, int64_t e0, int64_t e1,
                          const Sched& sc, hipStream_t s);
 hipError_t tuned_correct(const TunedData& t, int precision, int N, int c0, int c1, int64_t e0, int64_t e1,

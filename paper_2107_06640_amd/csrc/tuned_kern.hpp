@@ -185,37 +185,6 @@ __device__ __forceinline__ void star_q(float cx, float cy, float cz, float lam, 
   }
 }
 
-// Minus the Godunov flux A-hat^-(n) q^b at one face node (Sec. 4.2), with the
-// middle state a linear map of the given trace: c = n_x, n_y, n_z, then the
-// eight scaled coefficients of (s_n^b, v_n^b) from (s_n, v_n) and
-// (t_t^b, v_t^b) from (t_t, v_t).
-__device__ __forceinline__ void node_flux(const float* c, float lam, float mu, float rinv, const float* in,
-                                          float* out) {
-  const float nx = c[0], ny = c[1], nz = c[2];
-  const float tx = in[0] * nx + in[3] * ny + in[5] * nz;
-  const float ty = in[3] * nx + in[1] * ny + in[4] * nz;
-  const float tz = in[5] * nx + in[4] * ny + in[2] * nz;
-  const float sn = tx * nx + ty * ny + tz * nz;
-  const float ttx = tx - sn * nx, tty = ty - sn * ny, ttz = tz - sn * nz;
-  const float vn = in[6] * nx + in[7] * ny + in[8] * nz;
-  const float vtx = in[6] - vn * nx, vty = in[7] - vn * ny, vtz = in[8] - vn * nz;
-  const float snb = c[3] * sn + c[4] * vn;
-  const float vnb = c[5] * sn + c[6] * vn;
-  const float tbx = c[7] * ttx + c[8] * vtx, tby = c[7] * tty + c[8] * vty, tbz = c[7] * ttz + c[8] * vtz;
-  const float vbx = c[9] * ttx + c[10] * vtx, vby = c[9] * tty + c[10] * vty, vbz = c[9] * ttz + c[10] * vtz;
-  const float w = 2.0f * vnb;
-  // out is minus the flux (the sign every caller applies), so no sign flips
-  out[0] = lam * vnb + mu * (w * nx * nx + 2.0f * vbx * nx);
-  out[1] = lam * vnb + mu * (w * ny * ny + 2.0f * vby * ny);
-  out[2] = lam * vnb + mu * (w * nz * nz + 2.0f * vbz * nz);
-  out[3] = mu * (w * nx * ny + vbx * ny + vby * nx);
-  out[4] = mu * (w * ny * nz + vby * nz + vbz * ny);
-  out[5] = mu * (w * nx * nz + vbx * nz + vbz * nx);
-  out[6] = rinv * (snb * nx + tbx);
-  out[7] = rinv * (snb * ny + tby);
-  out[8] = rinv * (snb * nz + tbz);
-}
-
 // node_flux for the rows an element of the 4-quantity form carries (AC: s_xx,
 // where mu = 0 leaves lam v_n^b, and the velocity), from a trace of that form
 // (IN_AC: traction s_xx n) or a full trace (the neighbour's trace: elastic at
