@@ -57,7 +57,9 @@ struct DevData {
   // reference matrices (compute type)
   const T* K;   // [3][B][B]
   const T* Ef;  // [4][Bf][B]
-  const T* Lf;  // [4][B][Bf]
+  const T* Kt;  // [3][B][B] K^d transposed
+  const T* Et;  // [4][B][Bf] face traces, node-contiguous
+  const T* Lt;  // [4][Bf][B] lifts, row-contiguous
   const int32_t* perm;  // [6][Bf]
   // gravity (FP64)
   const double* Egt;    // [4][B][nq] traces at the eta points of a face, point-contiguous

@@ -26,28 +26,160 @@ namespace {
 // the same whichever launch covers it.
 constexpr int NT_WIDE = 256, NT_TALL = 1024, TALL_BELOW = 256;
 
+// LDS rows of nine quantities are three padded triples, each one wide read. A
+// contraction item is a (row, triple) whose sums run side by side; GROUP items
+// that read the same LDS rows (the directions of K, faces, two row halves) share
+// a thread where there are elements enough to fill the chip, so that a read of
+// LDS feeds 3 GROUP products: what bounds these loops is the return path of
+// LDS and of the matrices' loads, not the products. A launch over a few elements keeps
+// one item per thread. Matrices are indexed with the row contiguous, one coalesced
+// load. Every sum runs in ascending order on its own, however the
+// items are shared out.
+constexpr int kPad = 12;
+__device__ __forceinline__ int padded(int row, int p) { return row * kPad + p / 3 * 4 + p % 3; }
+
+template <typename T>
+struct alignas(4 * sizeof(T)) Triple {
+  T v[4];
+};
+
+// acc[u][j] += sum_l m[u][l ld] row_l[j], l < n, of the triple at x
+template <int GROUP, typename T>
+__device__ __forceinline__ void chain(T (&acc)[GROUP][3], const T* const (&m)[GROUP], int ld, const T* x, int n) {
+#pragma unroll (GROUP == 1 ? 16 : 8)
+  for (int l = 0; l < n; ++l) {
+    const Triple<T> r = *reinterpret_cast<const Triple<T>*>(x + l * kPad);
+#pragma unroll
+    for (int u = 0; u < GROUP; ++u) {
+      const T k = m[u][l * ld];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) acc[u][j] += k * r.v[j];
+    }
+  }
+}
+// the same, subtracted
+template <int GROUP, typename T>
+__device__ __forceinline__ void chain_sub(T (&acc)[GROUP][3], const T* const (&m)[GROUP], int ld, const T* x, int n) {
+#pragma unroll (GROUP == 1 ? 16 : 8)
+  for (int l = 0; l < n; ++l) {
+    const Triple<T> r = *reinterpret_cast<const Triple<T>*>(x + l * kPad);
+#pragma unroll
+    for (int u = 0; u < GROUP; ++u) {
+      const T k = m[u][l * ld];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) acc[u][j] -= k * r.v[j];
+    }
+  }
+}
+
+// Y_d = (K^d)^T D (rows below nout), GROUP directions per thread
+template <int GROUP, typename T, int N>
+__device__ __forceinline__ void plain_level(const DevData<T>& d, const T* sD, T* sY, int nin, int nout) {
+  constexpr int B = nbasis(N), B1 = nbasis(N - 1);
+  for (int i = threadIdx.x; i < 9 / GROUP * nout; i += blockDim.x) {
+    const int gp = i / nout, m = i - gp * nout, d0 = gp / 3 * GROUP, pg = gp % 3;
+    T acc[GROUP][3] = {};
+    const T* K[GROUP];
+#pragma unroll
+    for (int u = 0; u < GROUP; ++u) K[u] = d.K + (size_t)(d0 + u) * B * B + m;
+    chain<GROUP, T>(acc, K, B, sD + pg * 4, nin);
+#pragma unroll
+    for (int u = 0; u < GROUP; ++u)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) sY[((d0 + u) * B1 + m) * kPad + pg * 4 + j] = acc[u][j];
+  }
+}
+
+// traces of s at the face nodes, GROUP faces per thread
+template <int GROUP, typename T, int N>
+__device__ __forceinline__ void plain_trace(const DevData<T>& d, const T* s, T* sV) {
+  constexpr int B = nbasis(N), Bf = nface(N);
+  for (int i = threadIdx.x; i < 12 / GROUP * Bf; i += blockDim.x) {
+    const int gp = i / Bf, m = i % Bf, f0 = gp / 3 * GROUP, pg = gp % 3;
+    T acc[GROUP][3] = {};
+    const T* E[GROUP];
+#pragma unroll
+    for (int u = 0; u < GROUP; ++u) E[u] = d.Et + (size_t)(f0 + u) * B * Bf + m;
+    chain<GROUP, T>(acc, E, Bf, s + pg * 4, B);
+#pragma unroll
+    for (int u = 0; u < GROUP; ++u)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) sV[((f0 + u) * Bf + m) * kPad + pg * 4 + j] = acc[u][j];
+  }
+}
+
+// Q += volume term of sY (if VOLUME), then minus the lifts of the fluxes sF; GROUP rows per thread.
+template <int GROUP, bool VOLUME, typename T, int N>
+__device__ __forceinline__ void plain_lift(const DevData<T>& d, int64_t e, const T* sY, const T* sF) {
+  constexpr int B = nbasis(N), B1 = nbasis(N - 1), Bf = nface(N), RT = row_tiles(B), H = (B + GROUP - 1) / GROUP;
+  for (int i = threadIdx.x; i < 3 * H; i += blockDim.x) {
+    const int pg = i / H, k0 = i % H;
+    int row[GROUP];
+#pragma unroll
+    for (int u = 0; u < GROUP; ++u) row[u] = k0 + u * H < B ? k0 + u * H : B - 1;
+    T acc[GROUP][3] = {};
+    const T* M[GROUP];
+    if constexpr (VOLUME) {
+      for (int dd = 0; dd < 3; ++dd) {
+#pragma unroll
+        for (int u = 0; u < GROUP; ++u) M[u] = d.Kt + (size_t)dd * B * B + row[u];
+        chain<GROUP, T>(acc, M, B, sY + dd * B1 * kPad + pg * 4, B1);
+      }
+    }
+    // the faces follow one another
+#pragma unroll
+    for (int u = 0; u < GROUP; ++u) M[u] = d.Lt + row[u];
+    if constexpr (VOLUME)
+      chain_sub<GROUP, T>(acc, M, B, sF + pg * 4, 4 * Bf);
+    else
+      chain<GROUP, T>(acc, M, B, sF + pg * 4, 4 * Bf);
+#pragma unroll
+    for (int u = 0; u < GROUP; ++u) {
+      if (k0 + u * H >= B) continue;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        T& q = d.Q[qidx(e, row[u], pg * 3 + j, RT)];
+        if constexpr (VOLUME)
+          q += acc[u][j];
+        else
+          q -= acc[u][j];
+      }
+    }
+  }
+}
+
+// Predictor of one element. 1971 elements at order 6 in FP32: 122 us with one
+// product per read of LDS and of the matrices, 103 us in this form (corrector:
+// 35 and 33 us).
 template <typename T, int N>
 __global__ __launch_bounds__(NT_TALL) void k_predict_plain(DevData<T> d, int64_t e0, Sched sc) {
   const int NT = blockDim.x;
+  const bool tall = NT == NT_TALL;
   constexpr int B = nbasis(N), Bf = nface(N);
   constexpr int B1 = nbasis(N - 1);
   constexpr int RT = row_tiles(B), FT = row_tiles(Bf);
+  static_assert(4 * Bf >= B, "the derivative takes the traces' place");
   const int64_t e = e0 + blockIdx.x;
   const int parity = sc.parity(e);
   const int tid = threadIdx.x;
-  __shared__ T sD[B * 9], sI[B * 9], sIh[B * 9];
-  __shared__ T sY[3 * B * 9];  // reused for the volume term
-  __shared__ T sV[4 * Bf * 9], sVh[4 * Bf * 9];
+  __shared__ alignas(32) T sV[4 * Bf * kPad], sVh[4 * Bf * kPad];
+  __shared__ alignas(32) T sI[B * kPad], sIh[B * kPad];
+  __shared__ alignas(32) T sY[3 * B1 * kPad];  // reused for the volume term
   __shared__ T sG[9], sM[3];
+  T* sD = sV;  // until the traces
   if (tid < 9) sG[tid] = d.G[e * 9 + tid];
   if (tid < 3) sM[tid] = d.mat[e * 3 + tid];
   const int gs = d.dslot[e];
   T* gD = gs >= 0 ? d.gD + (int64_t)gs * (N + 1) * B * 9 : nullptr;
+  // the half-step integral, for a face towards a finer neighbour
+  bool finer = false;
+  for (int f = 0; f < 4; ++f) finer = finer || d.mode[e * 4 + f] == 2;
   for (int i = tid; i < B * 9; i += NT) {
     const T q = d.Q[qidx(e, i / 9, i % 9, RT)];
-    sD[i] = q;
-    sI[i] = q;
-    sIh[i] = q;
+    const int x = padded(i / 9, i % 9);
+    sD[x] = q;
+    sI[x] = q;
+    sIh[x] = q;
     if (gD) gD[i] = q;
   }
   __syncthreads();
@@ -56,47 +188,37 @@ __global__ __launch_bounds__(NT_TALL) void k_predict_plain(DevData<T> d, int64_t
   for (int k = 0; k < N; ++k) {
     const int nin = nbasis(N - k), nout = nbasis(N - k - 1);
     // Y_d = (K^d)^T D_k restricted to the non-zero rows
-    for (int i = tid; i < 3 * nout * 9; i += NT) {
-      const int dd = i / (nout * 9), m = (i / 9) % nout, r = i % 9;
-      const T* Kd = d.K + (size_t)dd * B * B;
-      T acc = T(0);
-#pragma unroll 8
-      for (int l = 0; l < nin; ++l) acc += Kd[l * B + m] * sD[l * 9 + r];
-      sY[(dd * B + m) * 9 + r] = acc;
-    }
+    if (tall)
+      plain_level<1, T, N>(d, sD, sY, nin, nout);
+    else
+      plain_level<3, T, N>(d, sD, sY, nin, nout);
     __syncthreads();
     const T f = T(-1) / T(k + 1);
     for (int i = tid; i < nout * 9; i += NT) {
       const int m = i / 9, p = i % 9;
       T wx[9], wy[9], wz[9];
       for (int r = 0; r < 9; ++r) {
-        const T y0 = sY[(0 * B + m) * 9 + r], y1 = sY[(1 * B + m) * 9 + r], y2 = sY[(2 * B + m) * 9 + r];
+        const T y0 = sY[padded(0 * B1 + m, r)], y1 = sY[padded(1 * B1 + m, r)], y2 = sY[padded(2 * B1 + m, r)];
         wx[r] = sG[0] * y0 + sG[3] * y1 + sG[6] * y2;
         wy[r] = sG[1] * y0 + sG[4] * y1 + sG[7] * y2;
         wz[r] = sG[2] * y0 + sG[5] * y1 + sG[8] * y2;
       }
       const T v = f * grad_op(p, lam, mu, rinv, wx, wy, wz);
-      sD[i] = v;
-      sI[i] += v / T(k + 2);
-      sIh[i] += v * half / T(k + 2);
-      if (gD) gD[(k + 1) * B * 9 + i] = v;  // rows below B_{N-k-1}: the others are not read
+      const int x = padded(m, p);
+      sD[x] = v;
+      sI[x] += v / T(k + 2);
+      sIh[x] += v * half / T(k + 2);
+      if (gD) gD[(k + 1) * B * 9 + i] = v;  // rows below B_{N-k-1}: the others are zero
     }
     half *= T(0.5);
     __syncthreads();
   }
   // traces at the face nodes: full step and first half step
-  for (int i = tid; i < 4 * Bf * 9; i += NT) {
-    const int f = i / (Bf * 9), m = (i / 9) % Bf, p = i % 9;
-    const T* Em = d.Ef + ((size_t)f * Bf + m) * B;
-    T a = T(0), b = T(0);
-#pragma unroll 8
-    for (int l = 0; l < B; ++l) {
-      a += Em[l] * sI[l * 9 + p];
-      b += Em[l] * sIh[l * 9 + p];
-    }
-    sV[i] = a;
-    sVh[i] = b;
-  }
+  if (tall)
+    plain_trace<1, T, N>(d, sI, sV);
+  else
+    plain_trace<2, T, N>(d, sI, sV);
+  if (finer) plain_trace<2, T, N>(d, sIh, sVh);
   __syncthreads();
   // hand the traces to the neighbours (in their node numbering)
   for (int i = tid; i < 4 * Bf * 9; i += NT) {
@@ -104,62 +226,52 @@ __global__ __launch_bounds__(NT_TALL) void k_predict_plain(DevData<T> d, int64_t
     const int md = d.mode[e * 4 + f];
     if (md == 0) continue;
     const int32_t t = d.tgt[e * 4 + f];
-    const int src = d.perm[d.hperm[e * 4 + f] * Bf + m];
-    const T v = sV[(f * Bf + src) * 9 + p];
+    const int src = padded(f * Bf + d.perm[d.hperm[e * 4 + f] * Bf + m], p);
+    const T v = sV[src];
     T* dst = d.In + inidx(t >> 2, t & 3, m, p, FT);
     if (md == 1) {
       *dst = v;
     } else if (md == 2) {
-      const T h1 = sVh[(f * Bf + src) * 9 + p];  // first half-step integral over the receiver's dt
+      const T h1 = sVh[src];  // first half-step integral over the receiver's dt
       *dst = h1;
       d.H2[((int64_t)d.half2[e * 4 + f] * Bf + m) * 9 + p] = T(2) * v - h1;
     } else {
       *dst = parity ? *dst + T(0.5) * v : T(0.5) * v;
     }
   }
-  // local flux at the nodes: F~-_f V_f (in place into sVh)
+  // local flux at the nodes: F~-_f V_f (into sVh)
   __syncthreads();
   for (int i = tid; i < 4 * Bf * 9; i += NT) {
     const int f = i / (Bf * 9), m = (i / 9) % Bf, p = i % 9;
     const T* F = d.Fm + ((e * 4 + f) * 81 + p * 9);
     T a = T(0);
-    for (int r = 0; r < 9; ++r) a += F[r] * sV[(f * Bf + m) * 9 + r];
-    sVh[i] = a;
+    for (int r = 0; r < 9; ++r) a += F[r] * sV[padded(f * Bf + m, r)];
+    sVh[padded(f * Bf + m, p)] = a;
   }
   // volume: Z_d[l] = (dt A*_d) I~[l] for l < B1
   for (int i = tid; i < 3 * B1; i += NT) {
     const int dd = i / B1, l = i % B1;
-    T out[9];
-    apply_star(sG[dd * 3 + 0], sG[dd * 3 + 1], sG[dd * 3 + 2], lam, mu, rinv, &sI[l * 9], out);
-    for (int p = 0; p < 9; ++p) sY[(dd * B + l) * 9 + p] = out[p];
+    T in[9], out[9];
+    for (int p = 0; p < 9; ++p) in[p] = sI[padded(l, p)];
+    apply_star(sG[dd * 3 + 0], sG[dd * 3 + 1], sG[dd * 3 + 2], lam, mu, rinv, in, out);
+    for (int p = 0; p < 9; ++p) sY[padded(dd * B1 + l, p)] = out[p];
   }
   __syncthreads();
-  for (int i = tid; i < B * 9; i += NT) {
-    const int kk = i / 9, p = i % 9;
-    T acc = T(0);
-    for (int dd = 0; dd < 3; ++dd) {
-      const T* Kd = d.K + ((size_t)dd * B + kk) * B;
-#pragma unroll 8
-      for (int l = 0; l < B1; ++l) acc += Kd[l] * sY[(dd * B + l) * 9 + p];
-    }
-    for (int f = 0; f < 4; ++f) {
-      const T* L = d.Lf + ((size_t)f * B + kk) * Bf;
-#pragma unroll 8
-      for (int m = 0; m < Bf; ++m) acc -= L[m] * sVh[(f * Bf + m) * 9 + p];
-    }
-    d.Q[qidx(e, kk, p, RT)] += acc;
-  }
+  if (tall)
+    plain_lift<1, true, T, N>(d, e, sY, sVh);
+  else
+    plain_lift<2, true, T, N>(d, e, sY, sVh);
 }
 
 template <typename T, int N>
 __global__ __launch_bounds__(NT_TALL) void k_correct_plain(DevData<T> d, int64_t e0, Sched sc) {
   const int NT = blockDim.x;
-  constexpr int B = nbasis(N), Bf = nface(N);
-  constexpr int RT = row_tiles(B), FT = row_tiles(Bf);
+  constexpr int Bf = nface(N);
+  constexpr int FT = row_tiles(Bf);
   const int64_t e = e0 + blockIdx.x;
   const int parity = sc.parity(e);
   const int tid = threadIdx.x;
-  __shared__ T sW[4 * Bf * 9];
+  __shared__ alignas(32) T sW[4 * Bf * kPad];
   for (int i = tid; i < 4 * Bf * 9; i += NT) {
     const int f = i / (Bf * 9), m = (i / 9) % Bf, p = i % 9;
     const int h2 = d.rhalf2[e * 4 + f];
@@ -171,19 +283,13 @@ __global__ __launch_bounds__(NT_TALL) void k_correct_plain(DevData<T> d, int64_t
     } else {
       for (int r = 0; r < 9; ++r) a += F[r] * d.In[inidx(e, f, m, r, FT)];
     }
-    sW[i] = a;
+    sW[padded(f * Bf + m, p)] = a;
   }
   __syncthreads();
-  for (int i = tid; i < B * 9; i += NT) {
-    const int kk = i / 9, p = i % 9;
-    T acc = T(0);
-    for (int f = 0; f < 4; ++f) {
-      const T* L = d.Lf + ((size_t)f * B + kk) * Bf;
-#pragma unroll 8
-      for (int m = 0; m < Bf; ++m) acc += L[m] * sW[(f * Bf + m) * 9 + p];
-    }
-    d.Q[qidx(e, kk, p, RT)] -= acc;
-  }
+  if (NT == NT_TALL)
+    plain_lift<1, false, T, N>(d, e, nullptr, sW);
+  else
+    plain_lift<2, false, T, N>(d, e, nullptr, sW);
 }
 
 // Gravity face (Sec. 4.3): per point, the forcing f = v_n + p/Z of the

@@ -235,18 +235,13 @@ hipError_t group_build(GroupArgs<T>& a, TunedData& t, const Model& M, const DevD
     for (int64_t e : {int64_t(M.f_elem[k]), int64_t(M.f_pelem[k])}) ds[e] = M.dslot[e];
   for (int64_t e = 0; e < M.E; ++e)
     for (int f = 0; f < 4; ++f) mh[e] |= ((M.mode[e * 4 + f] & 3) | (M.hperm[e * 4 + f] & 7) << 2) << (8 * f);
-  const int B = n_basis(M.N), Bf = (M.N + 1) * (M.N + 2) / 2;
-  std::vector<double> Et(size_t(4) * B * Bf);
-  for (int f = 0; f < 4; ++f)
-    for (int m = 0; m < Bf; ++m)
-      for (int l = 0; l < B; ++l) Et[(size_t(f) * B + l) * Bf + m] = M.ref.E[(size_t(f) * Bf + m) * B + l];
-  T *rcm, *rcp, *ih, *img, *et;
+  const int B = n_basis(M.N);
+  T *rcm, *rcp, *ih, *img;
   int32_t *pinv, *dm, *dl, *hs, *fx, *runs;
   hipError_t st = alloc(owned, bytes, &rcm, M.E * 48);
   if (st == hipSuccess) st = alloc(owned, bytes, &rcp, M.E * 48);
   if (st == hipSuccess) st = alloc(owned, bytes, &ih, fl.slots * int64_t(row_tiles(B) * 36 * 64));
   if (st == hipSuccess) st = upload(owned, bytes, &img, group_image(M, sizeof(T) == 8));
-  if (st == hipSuccess) st = upload(owned, bytes, &et, Et);
   if (st == hipSuccess) st = upload(owned, bytes, &pinv, M.ref.pinv);
   if (st == hipSuccess) st = upload(owned, bytes, &dm, mh);
   if (st == hipSuccess) st = upload(owned, bytes, &dl, ds);
@@ -257,7 +252,7 @@ hipError_t group_build(GroupArgs<T>& a, TunedData& t, const Model& M, const DevD
   a.RCm = rcm;
   a.RCp = rcp;
   a.Ih = ih;
-  a.Et = et;
+  a.Et = d.Et;
   a.img = img;
   a.pinv = pinv;
   a.mh4 = dm;
