@@ -18,7 +18,7 @@ struct PointSet {
   int64_t n = 0;
   std::vector<double> xyz;           // [n][3]
   std::vector<int64_t> elem_caller;  // [n]
-  double* phi = nullptr;             // device [n][B]: basis values at the point's reference coordinates
+  double* phi = nullptr;             // device [B][n]: basis values at the point's reference coordinates
   int32_t* elem = nullptr;           // device [n]: element, library order
   bool sea = false;                  // the sea-surface set (the points of eta)
 };
@@ -35,7 +35,7 @@ std::string locate_points(const Model& M, int64_t n, const double* xyz, std::vec
 std::string build_points(const Model& M, int which, int64_t n, const double* xyz, PointSet& ps,
                          std::vector<double>& phi, std::vector<int32_t>& elem_lib);
 
-// out[r][p] = sum_l phi[r][l] Q[elem[r]][l][p] (FP64); eta_out[r] = eta[r] if eta_out.
+// out[r][p] = sum_l phi[l][r] Q[elem[r]][l][p] (FP64); eta_out[r] = eta[r] if eta_out.
 hipError_t launch_sample(const PointSet& ps, int B, const double* Q64, const float* Q32, const double* eta,
                          double* out, double* eta_out, hipStream_t s);
 
