@@ -19,6 +19,7 @@
 #include "layout.hpp"
 #include "model.hpp"
 #include "probe.hpp"
+#include "state_io.hpp"
 #include "tuned.hpp"
 
 using namespace seis;
@@ -62,6 +63,7 @@ struct seis_t {
   DevData<float> d32{};
   TunedData tuned{};
   int32_t* glist = nullptr;             // gravity faces grouped by cluster
+  StateIO io;                           // transfers of the state to and from the caller
   std::vector<int64_t> gstart;          // [C+1]
   std::string err = "no error";
   // schedule cursor inside the current macro step
@@ -211,6 +213,9 @@ int build_common(seis_t* h, DevData<double>& c) {
   HIPCHK(h, upload(b, &gslot, M.gslot), "upload gslot");
   HIPCHK(h, upload(b, &dslot, M.dslot), "upload dslot");
   HIPCHK(h, upload(b, &perm, M.ref.perm), "upload perm");
+  int32_t* at;
+  HIPCHK(h, upload(b, &at, M.new_of_old), "upload element positions");
+  h->io.at = at;
   HIPCHK(h, upload(b, &Egt, transposed(M.ref.Eg, 4, M.nq, M.B)), "upload Eg");
   HIPCHK(h, upload(b, &Lgt, transposed(M.ref.Lg, 4, M.B, M.nq)), "upload Lg");
   std::vector<int32_t> ge(M.g_elem.begin(), M.g_elem.end());
@@ -639,21 +644,9 @@ int seis_write(seis_t* h, const double* dofs, const double* eta) {
   Model& M = h->M;
   HIPCHK(h, hipStreamSynchronize(h->stream), "sync");
   if (dofs) {
-    const int RT = row_tiles(M.B);
-    const int64_t n = q_size(M.E, RT);
-    const size_t row = (size_t)M.B * 9;
-    std::vector<double> tmp(n, 0.0);
-    for (int64_t k = 0; k < M.E; ++k) {
-      const double* src = dofs + M.old_of_new[k] * row;
-      for (int r = 0; r < M.B; ++r)
-        for (int p = 0; p < 9; ++p) tmp[qidx(k, r, p, RT)] = src[r * 9 + p];
-    }
-    if (h->precision == SEIS_FP64) {
-      HIPCHK(h, hipMemcpy(h->d64.Q, tmp.data(), n * sizeof(double), hipMemcpyHostToDevice), "write Q");
-    } else {
-      std::vector<float> tf(tmp.begin(), tmp.end());
-      HIPCHK(h, hipMemcpy(h->d32.Q, tf.data(), n * sizeof(float), hipMemcpyHostToDevice), "write Q");
-    }
+    const hipError_t st = h->precision == SEIS_FP64 ? state_write(h->io, h->d64.Q, dofs, M.E, M.B, h->stream)
+                                                    : state_write(h->io, h->d32.Q, dofs, M.E, M.B, h->stream);
+    HIPCHK(h, st, "write Q");
   }
   if (eta && !M.g_elem.empty()) {
     HIPCHK(h, hipMemcpy(h->d64.eta, eta, M.g_elem.size() * M.nq * sizeof(double), hipMemcpyHostToDevice),
@@ -897,22 +890,9 @@ int seis_read(seis_t* h, double* dofs, double* eta) {
   Model& M = h->M;
   HIPCHK(h, hipStreamSynchronize(h->stream), "sync");
   if (dofs) {
-    const int RT = row_tiles(M.B);
-    const int64_t n = q_size(M.E, RT);
-    const size_t row = (size_t)M.B * 9;
-    std::vector<double> tmp(n);
-    if (h->precision == SEIS_FP64) {
-      HIPCHK(h, hipMemcpy(tmp.data(), h->d64.Q, n * sizeof(double), hipMemcpyDeviceToHost), "read Q");
-    } else {
-      std::vector<float> tf(n);
-      HIPCHK(h, hipMemcpy(tf.data(), h->d32.Q, n * sizeof(float), hipMemcpyDeviceToHost), "read Q");
-      for (int64_t i = 0; i < n; ++i) tmp[i] = tf[i];
-    }
-    for (int64_t k = 0; k < M.E; ++k) {
-      double* dst = dofs + M.old_of_new[k] * row;
-      for (int r = 0; r < M.B; ++r)
-        for (int p = 0; p < 9; ++p) dst[r * 9 + p] = tmp[qidx(k, r, p, RT)];
-    }
+    const hipError_t st = h->precision == SEIS_FP64 ? state_read(h->io, h->d64.Q, dofs, M.E, M.B, h->stream)
+                                                    : state_read(h->io, h->d32.Q, dofs, M.E, M.B, h->stream);
+    HIPCHK(h, st, "read Q");
   }
   if (eta && !M.g_elem.empty()) {
     HIPCHK(h, hipMemcpy(eta, h->d64.eta, M.g_elem.size() * M.nq * sizeof(double), hipMemcpyDeviceToHost),
@@ -1139,6 +1119,7 @@ void seis_destroy(seis_t* h) {
   if (h->cap) (void)hipStreamDestroy(h->cap);
   for (hipEvent_t ev : h->pool) (void)hipEventDestroy(ev);
   if (h->en_partial) (void)hipFree(h->en_partial);
+  state_io_free(h->io);
   h->buf.release();
   delete h;
 }
