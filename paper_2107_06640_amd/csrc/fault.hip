@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kFaultThreads) void k_fault(FaultArgs a, const T* g
   constexpr int ND = (N + 1) * B * 9;      // stored values per element
   __shared__ T sd[2][ND];                  // derivatives D~k of the two sides
   __shared__ double tr[2][N + 1][Bf][9];   // their traces at the nodes
-  const int64_t f = f0 + blockIdx.x;
+  const int64_t f = f0 + xcd_block();
   const int64_t em = a.elem[f], ep = a.pelem[f];
   const int fm = a.face[f], fp = a.pface[f], h = a.perm[f];
   const T* Dm = gD + (int64_t)a.dslot[em] * ND;

@@ -20,7 +20,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_forcing(ForcingArgs a, T* In, int64_t f0) {
   constexpr int kChunk = 64;
   __shared__ double du[400], sr[kMaxUpliftSources], sp[36 * (kChunk + 1)];
-  const int64_t f = f0 + blockIdx.x;
+  const int64_t f = f0 + xcd_block();
   const double t1 = (double(*a.macro) * a.macro_len + a.sub + 1) * a.dt_min;
   const double dt = a.dt[f], t0 = t1 - dt;
   const int n = int(a.src[0]) < kMaxUpliftSources ? int(a.src[0]) : kMaxUpliftSources;

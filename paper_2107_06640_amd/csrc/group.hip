@@ -72,14 +72,6 @@ constexpr int kRow = 9 * 16;  // values of one row of 16 elements
 template <typename T, int N>
 constexpr int waves = N >= 5 || (N == 4 && sizeof(T) == 4) ? 8 : 4;
 
-__device__ __forceinline__ int64_t xcd_block() {
-  // XCD x (work-groups are dispatched round-robin over eight) takes a contiguous range of groups
-  const int64_t b = blockIdx.x, nb = gridDim.x;
-  if (nb < 8) return b;
-  const int64_t q = nb >> 3, r = nb & 7, x = b & 7, j = b >> 3;
-  return x < r ? x * (q + 1) + j : r * (q + 1) + (x - r) * q + j;
-}
-
 // A fragments of the first slabs of a contraction, requested before the barrier
 // that its rows wait for.
 constexpr int kAhead = 3;
@@ -582,7 +574,7 @@ __global__ __launch_bounds__(kFinerThreads) void k_finer_group(GroupArgs<T> a, i
   extern __shared__ __align__(16) unsigned char smem[];
   T* sI = reinterpret_cast<T*>(smem);  // tiled layout of the group
   T* sE = sI + D::SB * 9 * 64;         // [f][mode][node]
-  const int32_t* ent = a.fix_group + (first + blockIdx.x) * 3;
+  const int32_t* ent = a.fix_group + (first + xcd_block()) * 3;
   const int grp = ent[0], f0 = ent[1], nf = ent[2];
   auto stage = [&](T* dst, const T* src, int n) {
     for (int i = threadIdx.x; i < n * (int)sizeof(T) / 16; i += kFinerThreads)

@@ -149,8 +149,8 @@ __device__ __forceinline__ void plain_lift(const DevData<T>& d, int64_t e, const
 }
 
 // Predictor of one element. 1971 elements at order 6 in FP32: 122 us with one
-// product per read of LDS and of the matrices, 103 us in this form (corrector:
-// 35 and 33 us).
+// product per read of LDS and of the matrices, 103 us in this form, 91 us
+// with the elements of a group on one XCD (corrector: 35, 33 and 26 us).
 template <typename T, int N>
 __global__ __launch_bounds__(NT_TALL) void k_predict_plain(DevData<T> d, int64_t e0, Sched sc) {
   const int NT = blockDim.x;
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(NT_TALL) void k_predict_plain(DevData<T> d, int64_t
   constexpr int B1 = nbasis(N - 1);
   constexpr int RT = row_tiles(B), FT = row_tiles(Bf);
   static_assert(4 * Bf >= B, "the derivative takes the traces' place");
-  const int64_t e = e0 + blockIdx.x;
+  const int64_t e = e0 + xcd_block();
   const int parity = sc.parity(e);
   const int tid = threadIdx.x;
   __shared__ alignas(32) T sV[4 * Bf * kPad], sVh[4 * Bf * kPad];
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(NT_TALL) void k_correct_plain(DevData<T> d, int64_t
   const int NT = blockDim.x;
   constexpr int Bf = nface(N);
   constexpr int FT = row_tiles(Bf);
-  const int64_t e = e0 + blockIdx.x;
+  const int64_t e = e0 + xcd_block();
   const int parity = sc.parity(e);
   const int tid = threadIdx.x;
   __shared__ alignas(32) T sW[4 * Bf * kPad];
@@ -299,13 +299,13 @@ __global__ __launch_bounds__(NT_TALL) void k_correct_plain(DevData<T> d, int64_t
 // velocity rows g H n) lifted with the face rule. Bound by latency (traces,
 // the series, lifts, each behind a barrier): 1152 faces at order 6 took 50 us with
 // row-contiguous matrices, the zero rows of the derivatives and two FP64 divisions per
-// term, 42 us in this form.
+// term, 42 us in this form, 37 us with neighbouring faces on one XCD.
 template <typename T, int N>
 __global__ __launch_bounds__(256) void k_gravity(DevData<T> d, const int32_t* glist) {
   constexpr int B = nbasis(N);
   constexpr int RT = row_tiles(B);
   constexpr int nq = (N + 1) * (N + 1);
-  const int gf = glist[blockIdx.x];
+  const int gf = glist[xcd_block()];
   const int tid = threadIdx.x;
   const int64_t e = d.g_elem[gf];
   const int face = d.g_face[gf];

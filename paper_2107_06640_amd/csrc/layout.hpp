@@ -55,6 +55,18 @@ __host__ __device__ inline int64_t inidx(int64_t e, int f, int m, int p, int FT)
 // inverse.
 __host__ __device__ constexpr int tile_perm(int r) { return (r & ~15) | ((r & 3) << 2) | ((r >> 2) & 3); }
 
+// Logical work-group index of kernels with a work-group per element, face or
+// group. Work-groups are dispatched round-robin over eight XCDs, each with its own L2; XCD x takes a
+// contiguous range here, because the sixteen elements of a group share every
+// line of Q and of the inbox: spread over eight caches, each line would be fetched and
+// written back eight times.
+__device__ __forceinline__ int64_t xcd_block() {
+  const int64_t b = blockIdx.x, nb = gridDim.x;
+  if (nb < 8) return b;
+  const int64_t q = nb >> 3, r = nb & 7, x = b & 7, j = b >> 3;
+  return x < r ? x * (q + 1) + j : r * (q + 1) + (x - r) * q + j;
+}
+
 // Sizes (values) of the padded arrays for E elements.
 __host__ __device__ inline int64_t q_size(int64_t E, int RT) { return ((E + 15) >> 4) * RT * 4 * 9 * 64; }
 __host__ __device__ inline int64_t in_size(int64_t E, int FT) { return ((E + 15) >> 4) * 4 * FT * 4 * 9 * 64; }

@@ -23,7 +23,7 @@ template <int N>
 __global__ __launch_bounds__(64) void k_finer_fixup(TArgs a, const int32_t* list) {
   constexpr int B = nbasis(N), Bf = nface(N), FT = row_tiles(Bf);
   __shared__ float sIh[B * 9];
-  const int id = list[blockIdx.x];
+  const int id = list[xcd_block()];
   const int64_t e = id >> 2;
   const int f = id & 3;
   const float* D = a.gD + (int64_t)a.dslot[e] * (N + 1) * B * 9;
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(64) void k_finer_fixup(TArgs a, const int32_t* list
 template <int N>
 __global__ __launch_bounds__(64) void k_h2_to_in(TArgs a, const int32_t* list) {
   constexpr int Bf = nface(N), FT = row_tiles(Bf);
-  const int id = list[blockIdx.x];
+  const int id = list[xcd_block()];
   const int64_t e = id >> 2;
   const int f = id & 3;
   const int slot = a.rhalf2[e * 4 + f];
