@@ -19,12 +19,15 @@ namespace seis {
 
 namespace {
 
-// Threads per element: 256 for throughput; a launch over a few elements (a
-// tiny LTS cluster) is bound by the latency of one work-group, so it uses 1024.
+// Threads per element: 128 for throughput, as many as the longest loops have
+// items, so that more work-groups share a CU (a pass of BF16 steps whose finest cluster of 1971
+// elements runs here took 8.76 ms; 192 and 256 threads 9.05, 512 10.0); a launch
+// over a few elements (a tiny LTS cluster) is bound by the latency of one
+// work-group, so it uses 1024.
 // The thread count is a launch parameter of one compiled kernel, not a
 // template argument, so that an element's arithmetic (and its rounding) is
 // the same whichever launch covers it.
-constexpr int NT_WIDE = 256, NT_TALL = 1024, TALL_BELOW = 256;
+constexpr int NT_WIDE = 128, NT_TALL = 1024, TALL_BELOW = 256;
 
 // LDS rows of nine quantities are three padded triples, each one wide read. A
 // contraction item is a (row, triple) whose sums run side by side; GROUP items
@@ -43,10 +46,11 @@ struct alignas(4 * sizeof(T)) Triple {
   T v[4];
 };
 
-// acc[u][j] += sum_l m[u][l ld] row_l[j], l < n, of the triple at x
+// acc[u][j] += sum_l m[u][l ld] row_l[j], l < n, of the triple at x. Eight modes
+// are requested together (four: 1.5% on that pass; sixteen in the one-item form: 15% slower)
 template <int GROUP, typename T>
 __device__ __forceinline__ void chain(T (&acc)[GROUP][3], const T* const (&m)[GROUP], int ld, const T* x, int n) {
-#pragma unroll (GROUP == 1 ? 16 : 8)
+#pragma unroll 8
   for (int l = 0; l < n; ++l) {
     const Triple<T> r = *reinterpret_cast<const Triple<T>*>(x + l * kPad);
 #pragma unroll
@@ -60,7 +64,7 @@ __device__ __forceinline__ void chain(T (&acc)[GROUP][3], const T* const (&m)[GR
 // the same, subtracted
 template <int GROUP, typename T>
 __device__ __forceinline__ void chain_sub(T (&acc)[GROUP][3], const T* const (&m)[GROUP], int ld, const T* x, int n) {
-#pragma unroll (GROUP == 1 ? 16 : 8)
+#pragma unroll 8
   for (int l = 0; l < n; ++l) {
     const Triple<T> r = *reinterpret_cast<const Triple<T>*>(x + l * kPad);
 #pragma unroll
