@@ -13,42 +13,84 @@ namespace seis {
 
 namespace {
 
-// Half-step fix-up of the faces handing over to a finer neighbour (one
-// work-group per face of list): the predictor wrote the full-step trace V;
-// the finer neighbour needs the traces of the first and of the second half of
-// this element's step, each over its own step: the first half
-// h1 = E_f I~_h with I~_h = sum_k D~k 2^-k / (k+1) (from the stored
-// derivatives) goes to the inbox, the second half 2 V - h1 to its slot.
+// Half-step fix-up of the faces handing over to a finer neighbour: the
+// predictor wrote the full-step trace V; the finer neighbour needs the traces of
+// the first and of the second half of this element's step, each over its own
+// step: the first half h1 = E_f I~_h with I~_h = sum_k D~k 2^-k / (k+1) (from the
+// stored derivatives) goes to the inbox, the second half 2 V - h1 to its slot.
+// kFixElems elements share a work-group and its copy of the trace matrices; a
+// wavefront forms the I~_h of whole elements (the non-zero rows of the
+// derivatives, B_{N-k} of derivative k, requested together), then a thread sums
+// all nine quantities of a node (one value of E_f and three wide broadcasts of
+// I~_h per mode), V requested before. Bound by the memory traffic of the
+// derivatives and the two traces, and the latency of their addresses.
+// 248 832 elements at order 6 with four clusters (87 506 such faces): a pass of
+// two macro steps took 12.15 ms with a work-group of one wavefront per face, which
+// read all N + 1 full derivatives and its own copy of E_f, and 11.97 in this form.
+constexpr int kFixElems = 4, kFixThreads = 256;
+
 template <int N>
-__global__ __launch_bounds__(64) void k_finer_fixup(TArgs a, const int32_t* list) {
-  constexpr int B = nbasis(N), Bf = nface(N), FT = row_tiles(Bf);
-  __shared__ float sIh[B * 9];
-  const int id = list[xcd_block()];
-  const int64_t e = id >> 2;
-  const int f = id & 3;
-  const float* D = a.gD + (int64_t)a.dslot[e] * (N + 1) * B * 9;
-  for (int i = threadIdx.x; i < B * 9; i += 64) {
-    float acc = 0.0f, w = 1.0f;
-    for (int k = 0; k <= N; ++k) {
-      acc += w / float(k + 1) * D[k * B * 9 + i];
-      w *= 0.5f;
+__global__ __launch_bounds__(kFixThreads) void k_finer_fixup(TArgs a, const float* Et, const int32_t* runs, int64_t n) {
+  constexpr int B = nbasis(N), Bf = nface(N), FT = row_tiles(Bf), P = 12;  // P: a row of nine in three padded triples
+  __shared__ __align__(16) float sE[4 * B * Bf], sIh[kFixElems][B * P];
+  __shared__ int sOwner[4 * kFixElems], sId[4 * kFixElems], sSlot[kFixElems];
+  const int64_t r0 = xcd_block() * kFixElems;
+  const int ne = n - r0 < kFixElems ? int(n - r0) : kFixElems, tid = threadIdx.x;
+  // faces of the elements: consecutive entries of the list
+  const int f0 = runs[2 * r0], nf = runs[2 * (r0 + ne)] - f0;
+  if (tid < ne) {
+    sSlot[tid] = runs[2 * (r0 + tid) + 1];
+    for (int u = runs[2 * (r0 + tid)] - f0; u < runs[2 * (r0 + tid + 1)] - f0; ++u) sOwner[u] = tid;
+  }
+  if (tid < nf) sId[tid] = a.fix_list[f0 + tid];
+  for (int i = tid; i < 4 * B * Bf / 4; i += kFixThreads)
+    reinterpret_cast<f4*>(sE)[i] = reinterpret_cast<const f4*>(Et)[i];
+  __syncthreads();
+  for (int r = tid >> 6; r < ne; r += kFixThreads / 64) {
+    const float* D = a.gD + (int64_t)sSlot[r] * (N + 1) * B * 9;
+#pragma unroll 4
+    for (int j = tid & 63; j < B * 9; j += 64) {
+      const int row = j / 9, q = j - row * 9;
+      float d[N + 1], acc = 0.0f, w = 1.0f;
+#pragma unroll
+      for (int k = 0; k <= N; ++k) d[k] = row < nbasis(N - k) ? D[k * B * 9 + j] : 0.0f;
+#pragma unroll
+      for (int k = 0; k <= N; ++k) {
+        acc = __builtin_fmaf(w / float(k + 1), d[k], acc);
+        w *= 0.5f;
+      }
+      sIh[r][row * P + q / 3 * 4 + q % 3] = acc;
     }
-    sIh[i] = acc;
   }
   __syncthreads();
-  const int32_t tg = a.tgt[e * 4 + f];
-  const int h = a.hperm[e * 4 + f];
-  const int slot = a.half2[e * 4 + f];
-  for (int i = threadIdx.x; i < Bf * 9; i += 64) {
-    const int m = i / 9, p = i % 9;
-    const float* Em = a.Ef + ((int64_t)f * Bf + m) * B;
-    float h1 = 0.0f;
-    for (int l = 0; l < B; ++l) h1 += Em[l] * sIh[l * 9 + p];
-    const int mr = a.pinv[h * Bf + m];
-    float* dst = a.In + inidx(tg >> 2, tg & 3, mr, p, FT);
-    const float v = *dst;
-    *dst = h1;
-    a.H2[((int64_t)slot * Bf + mr) * 9 + p] = 2.0f * v - h1;
+  for (int i = tid; i < nf * Bf; i += kFixThreads) {
+    const int u = i / Bf, m = i - u * Bf, id = sId[u], f = id & 3;
+    const int32_t tg = a.tgt[id];
+    const int mr = a.pinv[a.hperm[id] * Bf + m];
+    float* out = a.H2 + ((int64_t)a.half2[id] * Bf + mr) * 9;
+    float* blk = a.In + in_block(tg >> 2, tg & 3, mr, FT) * 576;
+    const int l8 = in_lane(tg >> 2, mr);
+    f4* in = reinterpret_cast<f4*>(blk + 8 * l8);
+    const f4 v0 = in[0], v1 = in[1];
+    const float v8 = blk[512 + l8];
+    const float* E = sE + f * B * Bf + m;
+    const f4* I = reinterpret_cast<const f4*>(sIh[sOwner[u]]);
+    float h[9] = {};
+#pragma unroll 4
+    for (int l = 0; l < B; ++l) {
+      const float x = E[l * Bf];
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        const f4 y = I[l * 3 + t];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) h[t * 3 + j] = __builtin_fmaf(x, y[j], h[t * 3 + j]);
+      }
+    }
+    in[0] = f4{h[0], h[1], h[2], h[3]};
+    in[1] = f4{h[4], h[5], h[6], h[7]};
+    blk[512 + l8] = h[8];
+#pragma unroll
+    for (int p = 0; p < 9; ++p) out[p] = 2.0f * (p < 4 ? v0[p & 3] : (p < 8 ? v1[p & 3] : v8)) - h[p];
   }
 }
 
@@ -68,9 +110,10 @@ __global__ __launch_bounds__(64) void k_h2_to_in(TArgs a, const int32_t* list) {
 }
 
 template <int N>
-hipError_t launch_fixup(const TArgs& a, const int32_t* list, int64_t n, hipStream_t s) {
+hipError_t launch_fixup(const TunedData& t, int64_t first, int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_finer_fixup<N>, dim3((unsigned)n), dim3(64), 0, s, a, list);
+  hipLaunchKernelGGL(k_finer_fixup<N>, dim3((unsigned)((n + kFixElems - 1) / kFixElems)), dim3(kFixThreads), 0, s, t.a,
+                     t.d32.Et, t.fix_elem + 2 * first, n);
   return hipGetLastError();
 }
 
@@ -81,13 +124,14 @@ hipError_t launch_h2(const TArgs& a, const int32_t* list, int64_t n, hipStream_t
   return hipGetLastError();
 }
 
-hipError_t fixup_dispatch(int N, const TArgs& a, const int32_t* list, int64_t n, hipStream_t s) {
+// elements [first, first + n) of fix_elem
+hipError_t fixup_dispatch(int N, const TunedData& t, int64_t first, int64_t n, hipStream_t s) {
   switch (N) {
-    case 2: return launch_fixup<2>(a, list, n, s);
-    case 3: return launch_fixup<3>(a, list, n, s);
-    case 4: return launch_fixup<4>(a, list, n, s);
-    case 5: return launch_fixup<5>(a, list, n, s);
-    case 6: return launch_fixup<6>(a, list, n, s);
+    case 2: return launch_fixup<2>(t, first, n, s);
+    case 3: return launch_fixup<3>(t, first, n, s);
+    case 4: return launch_fixup<4>(t, first, n, s);
+    case 5: return launch_fixup<5>(t, first, n, s);
+    case 6: return launch_fixup<6>(t, first, n, s);
   }
   return hipErrorInvalidValue;
 }
@@ -270,7 +314,7 @@ hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevDat
   t.precision = precision;
   t.d64 = d64;
   t.d32 = d32;
-  t.fix_start = M.fix_start;
+  t.fix_start.assign(M.C + 1, 0);
   t.h2_start = M.h2_start;
   if (tile > 0) {
     const int w = tile <= 32 ? 2 : 4;
@@ -344,6 +388,20 @@ hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevDat
     if (st != hipSuccess) return st;
     a.dslot = ds;
     a.fix_list = fl;
+    // fix_list by element: the first entry of each and its slot of derivatives, and the end
+    std::vector<int32_t> fe;
+    for (int c = 0; c < M.C; ++c) {
+      t.fix_start[c] = (int64_t)fe.size() / 2;
+      for (int64_t i = M.fix_start[c]; i < M.fix_start[c + 1]; ++i)
+        if (i == M.fix_start[c] || M.fix_list[i] >> 2 != M.fix_list[i - 1] >> 2)
+          fe.insert(fe.end(), {int32_t(i), M.dslot[M.fix_list[i] >> 2]});
+    }
+    t.fix_start[M.C] = (int64_t)fe.size() / 2;
+    fe.insert(fe.end(), {int32_t(M.fix_list.size()), -1});
+    int32_t* dfe;
+    st = upload(owned, bytes, &dfe, fe);
+    if (st != hipSuccess) return st;
+    t.fix_elem = dfe;
     a.h2_list = hl;
   }
   {
@@ -429,8 +487,7 @@ hipError_t tuned_predict(const TunedData& t, int precision, int N, int c0, int c
   if (e1 - e0 < t.mc_min) return launch_predict_plain<float>(N, t.d32, e0, e1 - e0, sc, s);
   hipError_t st = pred_dispatch_any(precision, N, t.pc, t.a, e0, e1, sc, s);
   if (st != hipSuccess) return st;
-  const int64_t f0 = t.fix_start[c0], nf = t.fix_start[c1 + 1] - f0;
-  return fixup_dispatch(N, t.a, t.a.fix_list + f0, nf, s);
+  return fixup_dispatch(N, t, t.fix_start[c0], t.fix_start[c1 + 1] - t.fix_start[c0], s);
 }
 
 hipError_t tuned_correct(const TunedData& t, int precision, int N, int c0, int c1, int64_t e0, int64_t e1,

@@ -59,7 +59,8 @@ struct TunedData {
   int64_t mc_min = 0;    // ranges of fewer elements run on the FP32 group or plain kernels
   int64_t n_acoustic_groups = 0;  // 16-element groups run in the 4-quantity form
   TArgs a{};
-  std::vector<int64_t> fix_start, h2_start;  // per cluster: ranges of fix_list and h2_list
+  std::vector<int64_t> fix_start, h2_start;  // per cluster: ranges of fix_elem and h2_list
+  const int32_t* fix_elem = nullptr;         // [n + 1][2] first entry of fix_list of each element there, its dslot
   std::vector<int64_t> run_start;            // per cluster: ranges of the group arguments' fix_group
   GroupArgs<double> g64{};   // FP64
   GroupArgs<float> g32{};    // FP32 ranges below mc_min
