@@ -99,8 +99,8 @@ typedef struct {
 
 typedef struct {
   int precision;    /* SEIS_FP64 / SEIS_FP32 / SEIS_BF16 / SEIS_BF16_SPLIT (operands; FP32 accumulation) */
-  int kernel;       /* SEIS_KERNEL_TUNED (default) or SEIS_KERNEL_PLAIN; FP64 has no
-                       matrix-core form and always runs the plain kernels */
+  int kernel;       /* SEIS_KERNEL_TUNED (default) or SEIS_KERNEL_PLAIN. Tuned FP64 runs on the
+                       FP64 matrix cores at orders 3..6 and on the plain kernels elsewhere */
   double cfl;       /* C in dt_K = C/(2N+1) h_K / c_p,K (Sec. 4.4); default 0.35 */
   double g;         /* gravitational acceleration (Sec. 3); default 9.81 */
   int max_clusters; /* rate-2 LTS clusters (Sec. 4.4); 1 = global time stepping */
@@ -115,15 +115,16 @@ typedef struct {
                        SEIS_TUNE=w,cap,remap,w,cap,remap[,split[,shape]] fixes it. */
   int graph;        /* nonzero: seis_step captures its macro step into a hipGraph at its first
                        call and replays that graph afterwards (one launch per macro step) */
-  int mc_min;       /* tuned kernels, FP32/BF16: a cluster with fewer elements than this runs on
-                       the plain FP32 kernels instead of the matrix cores (a matrix-core
-                       wavefront works through its 16 elements in sequence, so a tiny cluster is
-                       bound by that latency there). Default 2048; 0 puts every cluster on the
-                       matrix cores. Must be >= 0. */
+  int mc_min;       /* tuned kernels, FP32/BF16: a cluster with fewer elements than this runs in
+                       FP32 in a form that gives its elements more of the chip (a wavefront of
+                       the form for large ranges works through 16 elements in sequence, so a
+                       small cluster is bound by that latency there): with FP32 operands a
+                       work-group per 16 elements from 256 elements on, else a work-group per
+                       element. Default 2048; 0 puts every cluster on the form for large ranges.
+                       Must be >= 0. */
   int fused;        /* nonzero (default): seis_step launches each phase of a sub-step once over every
                        cluster due in it (the due clusters 0..k are one element range, Sec. 4.4), the
-                       predictor over the range on the matrix cores when it has at least mc_min
-                       elements, else on the plain FP32 kernels; 0: one launch per cluster, each
+                       form chosen by the size of the range (mc_min); 0: one launch per cluster, each
                        cluster's kernel chosen by its own size. seis_predict/seis_correct always work
                        per cluster. */
   int acoustic;     /* tuned kernels, FP32/BF16: nonzero (default) runs each 16-element group whose
