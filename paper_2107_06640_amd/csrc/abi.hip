@@ -498,6 +498,11 @@ bool mid_step(const seis_t* h) {
   return false;
 }
 
+// The device's count of macro steps, read by the forcing alone: without a
+// prescribed-velocity face nobody reads it and its launch is left out (ten steps
+// of 1296 elements at order 3: 144 us with it, 129 without).
+hipError_t tick(seis_t* h) { return h->M.v_elem.empty() ? hipSuccess : launch_tick(h->macro_dev, h->stream); }
+
 // advance the cursor once every due predict and correct of the sub-step ran
 void maybe_advance(seis_t* h) {
   const int C = h->M.C;
@@ -516,7 +521,7 @@ void maybe_advance(seis_t* h) {
   if (h->sub == (1 << (C - 1))) {
     h->sub = 0;
     h->macro_done++;
-    (void)launch_tick(h->macro_dev, h->stream);
+    (void)tick(h);
   }
 }
 
@@ -803,7 +808,7 @@ int step_fused(seis_t* h) {
   }
   reset_cursor(h);
   h->macro_done++;
-  const hipError_t st = launch_tick(h->macro_dev, h->stream);
+  const hipError_t st = tick(h);
   if (st != hipSuccess) return hip_fail(h, st, "macro step counter");
   return SEIS_OK;
 }
