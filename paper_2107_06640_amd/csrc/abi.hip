@@ -276,7 +276,7 @@ int build_common(seis_t* h, DevData<double>& c) {
     const int64_t ns = std::max<int64_t>(F, 1) * M.Bf * kFaultState;
     HIPCHK(h, b.alloc(&h->fault_state, ns), "alloc fault state");
     HIPCHK(h, hipMemset(h->fault_state, 0, ns * sizeof(double)), "clear fault state");
-    HIPCHK(h, upload(b, &fE, M.ref.E), "upload face traces");
+    HIPCHK(h, upload(b, &fE, transposed(M.ref.E, 4, M.Bf, M.B)), "upload face traces");
     HIPCHK(h, upload(b, &pinv, M.ref.pinv), "upload node maps");
     std::vector<double> gx, gw;
     gauss_jacobi(M.N + 1, 0.0, 0.0, gx, gw);

@@ -53,7 +53,7 @@ struct FaultArgs {
   const double* geo;      // [F][8]: n, Zp-, Zs-, Zp+, Zs+, dt
   const double* par;      // [F][kFaultParams]
   double* state;          // [F][Bf][kFaultState]
-  const double* E;        // [4][Bf][B] basis at the face nodes
+  const double* Et;        // [4][B][Bf] face-trace matrices, node-contiguous
   const int32_t* pinv;    // [6][Bf]
   const int32_t* dslot;   // [E] slot of the stored time derivatives
   const double* tq;       // [N+1] Gauss-Legendre points on [0, 1]
