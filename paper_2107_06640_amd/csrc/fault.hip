@@ -62,11 +62,12 @@ __device__ inline double rs_steady_state(double V, const double* r) {
 // at node m, point after point. Bound by that serial chain of FP64 divisions and
 // roots on one wavefront, so it holds nothing that does
 // not depend on the point before (1152 faces at order 6, four macro steps of 55 296 elements: 2.47 ms with the
-// states formed inside it and row-contiguous matrices, 2.40 in this form).
+// states formed inside it and row-contiguous matrices, 2.40 in this form, 2.37 with
+// registers for three wavefronts per SIMD).
 constexpr int kFaultThreads = 256;
 
 template <typename T, int N>
-__global__ __launch_bounds__(kFaultThreads) void k_fault(FaultArgs a, const T* gD, T* In, int64_t f0) {
+__global__ __launch_bounds__(kFaultThreads, 3) void k_fault(FaultArgs a, const T* gD, T* In, int64_t f0) {
   constexpr int B = nbasis(N), Bf = nface(N), FT = row_tiles(Bf);
   constexpr int ND = (N + 1) * B * 9;      // stored values per element
   constexpr int NS = 2 * (N + 1) * Bf;     // (time point, side, node)

@@ -10,6 +10,14 @@
 // network). Only the weight gradients, sums over all points that nothing
 // rounds again, are summed in another order.
 //
+// Every stage is bound by reading and writing its activations. Measured on 64 samples of a
+// 64 x 64 x 32 grid, width 32, 12 modes, hidden width 128 (an activation is 1.07 GB; a large
+// copy moves 4.9 TB/s), average per call in a training step: k_idft_yt 854 us (two or
+// three activations, 2.5-3.8 TB/s), k_layer_bwd 1039 (three, 3.1), k_dft_ty 315 (one,
+// 3.4), k_dft_x 100, k_mix 108, k_mix_grad 94, k_pointwise 273, k_head 575 and k_head_bwd
+// 1944 (GELU and its derivative of 128 hidden values a point). The step takes 18.8 ms, with the general
+// products 160.5 ms; one sample's inference 0.35 and 2.15 ms.
+//
 // Fragment conventions (lane l, g = l / 16, c = l % 16): A holds row c, K
 // entries 8g..8g+7; B holds column c, the same K entries; the result holds
 // rows 4g..4g+3 of column c.
