@@ -52,7 +52,7 @@ hipError_t move(StateIO& io, double* dofs, int64_t E, int row, hipStream_t s, La
   const int64_t per = std::max<int64_t>(1, std::min<int64_t>(E, kChunkValues / row)), chunks = (E + per - 1) / per;
   const int hw = std::max(1, (int)std::thread::hardware_concurrency());
   const int workers = (int)std::min<int64_t>(std::min(kWorkers, hw), chunks);
-  const int64_t buf = per * row, need = buf * 2 * workers;
+  const int64_t buf = per * row, need = chunks == 1 ? buf : buf * 2 * workers;
   if (io.pin_values < need) {
     state_io_free(io);
     const hipError_t st = hipHostMalloc((void**)&io.pin, need * sizeof(double), hipHostMallocDefault);
