@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cmath>
 #include <sstream>
+#include <type_traits>
 
 #include "layout.hpp"
 #include "refelem.hpp"
@@ -33,15 +34,36 @@ void element_map(const Model& M, int64_t e, double x0[3], double Ji[9]) {
   for (int d = 0; d < 3; ++d) x0[d] = X[0][d];
 }
 
-// One thread per point, its nine sums side by side: neighbouring points lie in
-// neighbouring elements, so a wavefront reads the point-contiguous basis
-// values and, per quantity, the 64-byte rows of whole element groups. Bound by
-// reading the state once. The centroids of
-// 248 832 elements at order 6 and a sea surface took 261 us a call with a thread per
-// (point, quantity) and point-major basis values, 102 us in this form.
+// A sample is bound by the rows of the tiled state (and their pages) that a
+// load touches, and, for few points, by the wavefronts that share them out.
+// Two forms; every sum runs over the modes in ascending order in both.
+//
+// A thread per (point, quantity): 16 points by nine quantities per 144 threads.
+// Scattered receivers at order 6 in FP32, 256 / 4096 / 16 384 of them: 7 / 18 /
+// 61 us, with a thread per point 126 / 127 / 132 (64 rows and pages a load, a
+// ninth of the wavefronts).
 template <typename T>
-__global__ __launch_bounds__(256) void k_sample(const T* Q, int RT, int B, const int32_t* elem, const double* phi,
-                                                int64_t n, double* out, const double* eta, double* eta_out) {
+__global__ __launch_bounds__(192) void k_sample(const T* Q, int RT, int B, const int32_t* elem, const double* phi,
+                                               int64_t n, double* out, const double* eta, double* eta_out) {
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x, c = i / 144;
+  const int j = int(i - c * 144), p = j >> 4;
+  const int64_t r = c * 16 + (j & 15);
+  if (r >= n) return;
+  const T* q = Q + qidx(elem[r], 0, p, RT);
+  double acc = 0.0;
+#pragma unroll 8
+  for (int l = 0; l < B; ++l) acc += phi[l * n + r] * (double)q[(l >> 2) * 576 + (l & 3) * 16];
+  out[r * 9 + p] = acc;
+  if (p == 0 && eta_out) eta_out[r] = eta[r];
+}
+
+// A thread per point, its nine sums side by side, for large sets: the basis
+// values are read once, and a load touches a row per group of elements in the
+// wavefront's 64 points (launch_sample has the rule and the times).
+template <typename T>
+__global__ __launch_bounds__(256) void k_sample_wide(const T* Q, int RT, int B, const int32_t* elem,
+                                                      const double* phi, int64_t n, double* out, const double* eta,
+                                                      double* eta_out) {
   const int64_t r = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (r >= n) return;
   const int64_t e = elem[r];
@@ -56,6 +78,20 @@ __global__ __launch_bounds__(256) void k_sample(const T* Q, int RT, int B, const
 #pragma unroll
   for (int p = 0; p < 9; ++p) out[r * 9 + p] = acc[p];
   if (eta_out) eta_out[r] = eta[r];
+}
+
+// whether 64 consecutive points lie in at most 16 groups of elements on average
+bool in_order(const std::vector<int32_t>& elem) {
+  const int64_t n = (int64_t)elem.size();
+  int64_t groups = 0;
+  std::vector<int32_t> g;
+  for (int64_t r0 = 0; r0 < n; r0 += 64) {
+    g.clear();
+    for (int64_t r = r0; r < std::min(n, r0 + 64); ++r) g.push_back(elem[r] >> 4);
+    std::sort(g.begin(), g.end());
+    groups += std::unique(g.begin(), g.end()) - g.begin();
+  }
+  return groups * 4 <= n;
 }
 
 }  // namespace
@@ -196,6 +232,7 @@ std::string build_points(const Model& M, int which, int64_t n, const double* xyz
     for (int l = 0; l < B; ++l) phi[l * n + r] = row[l];
     elem_lib[r] = int32_t(M.new_of_old[ec[r]]);
   }
+  ps.ordered = in_order(elem_lib);
   return "";
 }
 
@@ -203,13 +240,25 @@ hipError_t launch_sample(const PointSet& ps, int B, const double* Q64, const flo
                          double* out, double* eta_out, hipStream_t s) {
   if (ps.n <= 0) return hipSuccess;
   const int RT = row_tiles(B);
-  const unsigned grid = (unsigned)((ps.n + 255) / 256);
+  // A thread per point from 20 480 points on if they follow the mesh, in FP64, whose
+  // rows are whole cache lines, from 32 768 on in any order. Thread per point / per sum:
+  // centroids of graded boxes, FP64 order 5, 23 562: 25 / 39 us, FP32 order 6, 72 576: 60 / 77;
+  // of regular boxes, FP32 order 6, 16 384: 21 / 16, 24 000: 16 / 13, 192 000: 99 / 133; scattered,
+  // FP32, 16 384: 208 / 79, 100 000: 589 / 463, FP64, 16 384: 167 / 124, 24 000: 170 / 187, 100 000: 429 / 763.
+  // Work-groups of a wavefront below 4096 points, where they reach more CUs (1024 points 7.5 us, 11 with
+  // three), of three above (4096 points 18 us, 20 with one).
+  const bool wide = ps.n >= (ps.ordered ? 20480 : 32768) && (ps.ordered || Q64);
+  const int64_t threads = wide ? ps.n : (ps.n + 15) / 16 * 144;
+  const int wg = wide ? 256 : (ps.n < 4096 ? 64 : 192);
+  auto launch = [&](const auto* Q) {
+    using T = std::remove_const_t<std::remove_reference_t<decltype(*Q)>>;
+    hipLaunchKernelGGL(wide ? k_sample_wide<T> : k_sample<T>, dim3((unsigned)((threads + wg - 1) / wg)), dim3(wg), 0, s,
+                       Q, RT, B, ps.elem, ps.phi, ps.n, out, eta, eta_out);
+  };
   if (Q64)
-    hipLaunchKernelGGL(k_sample<double>, dim3(grid), dim3(256), 0, s, Q64, RT, B, ps.elem, ps.phi, ps.n, out, eta,
-                       eta_out);
+    launch(Q64);
   else
-    hipLaunchKernelGGL(k_sample<float>, dim3(grid), dim3(256), 0, s, Q32, RT, B, ps.elem, ps.phi, ps.n, out, eta,
-                       eta_out);
+    launch(Q32);
   return hipGetLastError();
 }
 

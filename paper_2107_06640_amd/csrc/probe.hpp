@@ -21,6 +21,7 @@ struct PointSet {
   double* phi = nullptr;             // device [B][n]: basis values at the point's reference coordinates
   int32_t* elem = nullptr;           // device [n]: element, library order
   bool sea = false;                  // the sea-surface set (the points of eta)
+  bool ordered = false;              // neighbouring points lie in neighbouring elements
 };
 
 // Element (the lowest caller id among those containing the point, within
