@@ -35,10 +35,16 @@ constexpr int NT_WIDE = 128, NT_TALL = 1024, TALL_BELOW = 256;
 // a thread where there are elements enough to fill the chip, so that a read of
 // LDS feeds 3 GROUP products: what bounds these loops is the return path of
 // LDS and of the matrices' loads, not the products. A launch over a few elements keeps
-// one item per thread. Matrices are indexed with the row contiguous, one coalesced
+// one item per thread, and so do the orders whose longest loop has no more items
+// than the work-group threads (kOneItem): there sharing only lengthens the
+// chains. A step in FP32 of 600 / 29 478 elements, shared and one item per thread: order 3
+// 17.5 / 186 us and 15.0 / 167, order 4 23.0 / 303 and 20.4 / 268, order 5 34.6 / 507 and
+// 32.2 / 524. Matrices are indexed with the row contiguous, one coalesced
 // load. Every sum runs in ascending order on its own, however the
 // items are shared out.
 constexpr int kPad = 12;
+template <int N>
+constexpr bool kOneItem = 9 * nbasis(N - 1) <= NT_WIDE;  // orders 2..4
 __device__ __forceinline__ int padded(int row, int p) { return row * kPad + p / 3 * 4 + p % 3; }
 
 template <typename T>
@@ -94,12 +100,14 @@ __device__ __forceinline__ void plain_level(const DevData<T>& d, const T* sD, T*
   }
 }
 
-// traces of s at the face nodes, GROUP faces per thread
+// traces of the first sets of (s0, s1) at the face nodes, GROUP faces per thread
 template <int GROUP, typename T, int N>
-__device__ __forceinline__ void plain_trace(const DevData<T>& d, const T* s, T* sV) {
-  constexpr int B = nbasis(N), Bf = nface(N);
-  for (int i = threadIdx.x; i < 12 / GROUP * Bf; i += blockDim.x) {
-    const int gp = i / Bf, m = i % Bf, f0 = gp / 3 * GROUP, pg = gp % 3;
+__device__ __forceinline__ void plain_trace(const DevData<T>& d, int sets, const T* s0, T* sV0, const T* s1, T* sV1) {
+  constexpr int B = nbasis(N), Bf = nface(N), NI = 12 / GROUP * Bf;
+  for (int j = threadIdx.x; j < sets * NI; j += blockDim.x) {
+    const int i = j < NI ? j : j - NI, gp = i / Bf, m = i % Bf, f0 = gp / 3 * GROUP, pg = gp % 3;
+    const T* s = j < NI ? s0 : s1;
+    T* sV = j < NI ? sV0 : sV1;
     T acc[GROUP][3] = {};
     const T* E[GROUP];
 #pragma unroll
@@ -158,7 +166,7 @@ __device__ __forceinline__ void plain_lift(const DevData<T>& d, int64_t e, const
 template <typename T, int N>
 __global__ __launch_bounds__(NT_TALL) void k_predict_plain(DevData<T> d, int64_t e0, Sched sc) {
   const int NT = blockDim.x;
-  const bool tall = NT == NT_TALL;
+  const bool single = kOneItem<N> || NT == NT_TALL;
   constexpr int B = nbasis(N), Bf = nface(N);
   constexpr int B1 = nbasis(N - 1);
   constexpr int RT = row_tiles(B), FT = row_tiles(Bf);
@@ -175,9 +183,10 @@ __global__ __launch_bounds__(NT_TALL) void k_predict_plain(DevData<T> d, int64_t
   if (tid < 3) sM[tid] = d.mat[e * 3 + tid];
   const int gs = d.dslot[e];
   T* gD = gs >= 0 ? d.gD + (int64_t)gs * (N + 1) * B * 9 : nullptr;
-  // the half-step integral, for a face towards a finer neighbour
-  bool finer = false;
-  for (int f = 0; f < 4; ++f) finer = finer || d.mode[e * 4 + f] == 2;
+  // the half-step integral, for a face towards a finer neighbour (four loads in flight
+  // together: || would chain them)
+  const int8_t* md4 = d.mode + e * 4;
+  const bool finer = (md4[0] == 2) | (md4[1] == 2) | (md4[2] == 2) | (md4[3] == 2);
   for (int i = tid; i < B * 9; i += NT) {
     const T q = d.Q[qidx(e, i / 9, i % 9, RT)];
     const int x = padded(i / 9, i % 9);
@@ -193,7 +202,7 @@ __global__ __launch_bounds__(NT_TALL) void k_predict_plain(DevData<T> d, int64_t
   for (int k = 0; k < N; ++k) {
     const int nin = nbasis(N - k), nout = nbasis(N - k - 1);
     // Y_d = (K^d)^T D_k restricted to the non-zero rows
-    if (tall)
+    if (single)
       plain_level<1, T, N>(d, sD, sY, nin, nout);
     else
       plain_level<3, T, N>(d, sD, sY, nin, nout);
@@ -219,11 +228,10 @@ __global__ __launch_bounds__(NT_TALL) void k_predict_plain(DevData<T> d, int64_t
     __syncthreads();
   }
   // traces at the face nodes: full step and first half step
-  if (tall)
-    plain_trace<1, T, N>(d, sI, sV);
+  if (single)
+    plain_trace<1, T, N>(d, finer ? 2 : 1, sI, sV, sIh, sVh);
   else
-    plain_trace<2, T, N>(d, sI, sV);
-  if (finer) plain_trace<2, T, N>(d, sIh, sVh);
+    plain_trace<2, T, N>(d, finer ? 2 : 1, sI, sV, sIh, sVh);
   __syncthreads();
   // hand the traces to the neighbours (in their node numbering)
   for (int i = tid; i < 4 * Bf * 9; i += NT) {
@@ -262,7 +270,7 @@ __global__ __launch_bounds__(NT_TALL) void k_predict_plain(DevData<T> d, int64_t
     for (int p = 0; p < 9; ++p) sY[padded(dd * B1 + l, p)] = out[p];
   }
   __syncthreads();
-  if (tall)
+  if (single)
     plain_lift<1, true, T, N>(d, e, sY, sVh);
   else
     plain_lift<2, true, T, N>(d, e, sY, sVh);
@@ -291,7 +299,7 @@ __global__ __launch_bounds__(NT_TALL) void k_correct_plain(DevData<T> d, int64_t
     sW[padded(f * Bf + m, p)] = a;
   }
   __syncthreads();
-  if (NT == NT_TALL)
+  if (kOneItem<N> || NT == NT_TALL)
     plain_lift<1, false, T, N>(d, e, nullptr, sW);
   else
     plain_lift<2, false, T, N>(d, e, nullptr, sW);
@@ -387,22 +395,26 @@ __global__ __launch_bounds__(256) void k_gravity(DevData<T> d, const int32_t* gl
   }
 }
 
+// Threads per element of a launch over ne elements. The one-item orders have no loop of more
+// than some 300 items: 256 threads while latency bounds the launch, 128 beyond (order 3, a step in
+// FP32 with 128, 256, 512 and 1024 threads: 288 elements 14.2, 13.5, 13.6, 17.5 us; 1296 elements 16.6, 16.5,
+// 25, 41; 6000 elements 40, 50, 85, 151).
+template <int N>
+unsigned threads_for(int64_t ne) {
+  if (kOneItem<N>) return ne < 1024 ? 256 : NT_WIDE;
+  return ne < TALL_BELOW ? NT_TALL : NT_WIDE;
+}
+
 template <typename T, int N>
 hipError_t pred_n(const DevData<T>& d, int64_t e0, int64_t ne, const Sched& sc, hipStream_t s) {
   if (ne <= 0) return hipSuccess;
-  if (ne < TALL_BELOW)
-    hipLaunchKernelGGL((k_predict_plain<T, N>), dim3((unsigned)ne), dim3(NT_TALL), 0, s, d, e0, sc);
-  else
-    hipLaunchKernelGGL((k_predict_plain<T, N>), dim3((unsigned)ne), dim3(NT_WIDE), 0, s, d, e0, sc);
+  hipLaunchKernelGGL((k_predict_plain<T, N>), dim3((unsigned)ne), dim3(threads_for<N>(ne)), 0, s, d, e0, sc);
   return hipGetLastError();
 }
 template <typename T, int N>
 hipError_t corr_n(const DevData<T>& d, int64_t e0, int64_t ne, const Sched& sc, hipStream_t s) {
   if (ne <= 0) return hipSuccess;
-  if (ne < TALL_BELOW)
-    hipLaunchKernelGGL((k_correct_plain<T, N>), dim3((unsigned)ne), dim3(NT_TALL), 0, s, d, e0, sc);
-  else
-    hipLaunchKernelGGL((k_correct_plain<T, N>), dim3((unsigned)ne), dim3(NT_WIDE), 0, s, d, e0, sc);
+  hipLaunchKernelGGL((k_correct_plain<T, N>), dim3((unsigned)ne), dim3(threads_for<N>(ne)), 0, s, d, e0, sc);
   return hipGetLastError();
 }
 template <typename T, int N>
