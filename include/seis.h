@@ -100,7 +100,8 @@ typedef struct {
 typedef struct {
   int precision;    /* SEIS_FP64 / SEIS_FP32 / SEIS_BF16 / SEIS_BF16_SPLIT (operands; FP32 accumulation) */
   int kernel;       /* SEIS_KERNEL_TUNED (default) or SEIS_KERNEL_PLAIN. Tuned FP64 runs on the
-                       FP64 matrix cores at orders 3..6 and on the plain kernels elsewhere */
+                       FP64 matrix cores at orders 3..6, but for launches over a few hundred
+                       elements, and on the plain kernels elsewhere */
   double cfl;       /* C in dt_K = C/(2N+1) h_K / c_p,K (Sec. 4.4); default 0.35 */
   double g;         /* gravitational acceleration (Sec. 3); default 9.81 */
   int max_clusters; /* rate-2 LTS clusters (Sec. 4.4); 1 = global time stepping */
@@ -118,9 +119,9 @@ typedef struct {
   int mc_min;       /* tuned kernels, FP32/BF16: a cluster with fewer elements than this runs in
                        FP32 in a form that gives its elements more of the chip (a wavefront of
                        the form for large ranges works through 16 elements in sequence, so a
-                       small cluster is bound by that latency there): with FP32 operands a
-                       work-group per 16 elements from 256 elements on, else a work-group per
-                       element. Default 2048; 0 puts every cluster on the form for large ranges.
+                       small cluster is bound by that latency there): a work-group per element or,
+                       with FP32 operands and elements enough, a work-group per 16 elements.
+                       Default 2048; 0 puts every cluster on the form for large ranges.
                        Must be >= 0. */
   int fused;        /* nonzero (default): seis_step launches each phase of a sub-step once over every
                        cluster due in it (the due clusters 0..k are one element range, Sec. 4.4), the

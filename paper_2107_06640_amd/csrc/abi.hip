@@ -147,15 +147,16 @@ std::vector<double> transposed(const std::vector<double>& a, int n, int rows, in
 }
 
 // whether the handle runs kernels with pointwise flux coefficients (every tuned one), and
-// whether it runs plain ones, with rotated flux matrices (chosen, an order
-// the group kernels lack, or a small range in 32 bits)
+// the elements, from the first on, that it may run on plain ones, with rotated flux matrices: all in
+// 32 bits, and in FP64 all if chosen or for want of group kernels, else those of small ranges
 template <typename T>
 bool pointwise_form(const seis_t* h) {
   return h->kernel == SEIS_KERNEL_TUNED && group_order<T>(h->M.N);
 }
 template <typename T>
-bool plain_form(const seis_t* h) {
-  return !pointwise_form<T>(h) || h->precision != SEIS_FP64;
+int64_t matrix_elements(const seis_t* h) {
+  if (!pointwise_form<T>(h) || h->precision != SEIS_FP64) return h->M.E;
+  return plain_elements(h->M, h->precision, h->tuned.mc_min);
 }
 
 template <typename T>
@@ -173,7 +174,7 @@ int build_dev(seis_t* h, DevData<T>& d) {
   // operators: filled on the device by the assembly kernel
   HIPCHK(h, b.alloc(&G, E * 9), "alloc G");
   HIPCHK(h, b.alloc(&mat, E * 3), "alloc mat");
-  const int64_t nF = plain_form<T>(h) ? E * 4 * 81 : 0;
+  const int64_t nF = matrix_elements<T>(h) * 4 * 81;
   HIPCHK(h, b.alloc(&Fm, nF), "alloc Fm");
   HIPCHK(h, b.alloc(&Fp, nF), "alloc Fp");
   HIPCHK(h, b.alloc(&In, in_size(E, FT)), "alloc In");
@@ -328,9 +329,9 @@ int assemble_ops(seis_t* h) {
   // the operators of the forms that run
   auto assemble = [&](auto& d, const auto* rcm, const auto* rcp) {
     using T = std::remove_reference_t<decltype(*d.Q)>;
-    const bool plain = plain_form<T>(h), pointwise = pointwise_form<T>(h);
-    const AsmOutput<T> out{const_cast<T*>(d.G), const_cast<T*>(d.mat), plain ? const_cast<T*>(d.Fm) : nullptr,
-                           plain ? const_cast<T*>(d.Fp) : nullptr, pointwise ? const_cast<T*>(rcm) : nullptr,
+    const bool pointwise = pointwise_form<T>(h);
+    const AsmOutput<T> out{const_cast<T*>(d.G), const_cast<T*>(d.mat), const_cast<T*>(d.Fm), const_cast<T*>(d.Fp),
+                           matrix_elements<T>(h) * 4, pointwise ? const_cast<T*>(rcm) : nullptr,
                            pointwise ? const_cast<T*>(rcp) : nullptr};
     return launch_assemble(in, out, nullptr);
   };

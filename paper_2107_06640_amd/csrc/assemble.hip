@@ -44,7 +44,7 @@ __global__ __launch_bounds__(64) void k_assemble(AsmInput in, AsmOutput<T> out) 
     zsp = sqrt(m2 * r2);
   }
   const double n[3] = {in.nrm[id * 3 + 0], in.nrm[id * 3 + 1], in.nrm[id * 3 + 2]};
-  if (out.Fm) {
+  if (id < out.faces) {
     double A[81], Tr[81], Ti[81], Gm[81], Gp[81], X[81], Y[81];
     jacobian_x(lam, mu, rho, A);
     rotation(n, Tr, Ti);

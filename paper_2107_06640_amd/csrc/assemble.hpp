@@ -28,8 +28,9 @@ template <typename T>
 struct AsmOutput {
   T* G;        // [E][9]    dt * Jinv
   T* mat;      // [E][3]    lambda, mu, 1/rho
-  T* Fm;       // [E][4][81] 2 A dt/|J| * T A- G- T^-1 (own trace), nullable
-  T* Fp;       // [E][4][81] 2 A dt/|J| * T A- G+ T^-1 (neighbour trace), nullable
+  T* Fm;       // [faces][81] 2 A dt/|J| * T A- G- T^-1 (own trace)
+  T* Fp;       // [faces][81] 2 A dt/|J| * T A- G+ T^-1 (neighbour trace)
+  int64_t faces;  // leading faces (element * 4 + face) that Fm and Fp are formed for
   T* RCm;      // [E][4][12] pointwise middle-state coefficients, own trace, nullable
   T* RCp;      // [E][4][12] pointwise middle-state coefficients, neighbour trace, nullable
 };

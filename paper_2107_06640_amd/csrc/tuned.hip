@@ -314,6 +314,8 @@ hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevDat
   t.precision = precision;
   t.d64 = d64;
   t.d32 = d32;
+  t.finer = M.fix_start;
+  t.plain_end = plain_elements(M, precision, t.mc_min);
   t.fix_start.assign(M.C + 1, 0);
   t.h2_start = M.h2_start;
   if (tile > 0) {
@@ -456,35 +458,64 @@ hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevDat
   return hipSuccess;
 }
 
+// A launch of the wavefront form (mc_min) needs elements enough to fill the chip with a
+// wavefront per 16; a smaller one takes a work-group per 16 elements (group) where that keeps more
+// of the chip busy than a work-group per element (plain). Measured, us of one launch, plain - group:
+//   corrector, from 256 elements on: FP32 288 elements 0.9 (order 3) .. 3.5 (order 6), 1920 2.8 .. 12; FP64
+//     288 -0.3 .. 0.5, 1920 3 .. 22; 162 elements 0.2 .. -0.2 and -0.4 .. -5;
+//   predictor, FP32 from 256 on: 162 elements -0.3 (order 3) .. -27 (order 7), 288 0.2, -0.4, 2.9, -0.8, -3.9
+//     (orders 3..7), 720 0.6 .. 4.1, 1920 2.5 .. 67;
+//   predictor, FP64 from 896 on: 720 elements -1.1 .. -3.8, 900 -0.5, -1.8, 0.2, 6.6 (orders 3..6), 1080 0.2 .. 35;
+//   predictor with faces towards a finer neighbour, whose traces take a launch of their own, from
+//     1536 on: LTS boxes of 576, 900, 1296 elements -4 .. -33, 1903 -4 .. 32, 2304 -0.4 .. 72.
+// Small ranges of the BF16 precisions stay on the plain kernels: BF16 rounding amplifies another
+// order of the FP32 sums (one ulp in a few elements of a small cluster becomes 3e-4 of the
+// result in four steps).
 namespace {
+constexpr int64_t kGroupCorrect = 256, kGroupPredict32 = 256, kGroupPredict64 = 896, kGroupFiner = 1536;
+}  // namespace
 
-// FP32 ranges that run on the group kernels: too few elements to fill the chip
-// with a wavefront per 16 (mc_min), but enough groups to keep more of it busy
-// than the plain kernels' work-group per element. At order 6, predictor: 106 elements 26 us
-// plain and 46 us grouped (7 work-groups), 1971 elements 122 us and 50 us; 1296 at order 3
-// 12 us and 11 us. Small ranges of the BF16 precisions stay on the plain
-// kernels: BF16 rounding amplifies another order of the FP32 sums (one ulp in a few
-// elements of a small cluster becomes 3e-4 of the result in four steps).
-constexpr int64_t kGroupMin = 256;
-bool group_range(const TunedData& t, int precision, int64_t n) {
-  return precision == 1 && n >= kGroupMin && n < t.mc_min;
+Form launch_form(int precision, int N, int64_t mc_min, int64_t n, bool predictor, bool finer) {
+  if (precision != 0 && n >= mc_min) return Form::wave;
+  if (precision > 1 || (precision == 0 && !group_order<double>(N))) return Form::plain;
+  int64_t from = kGroupCorrect;
+  if (predictor) from = finer ? kGroupFiner : (precision == 0 ? kGroupPredict64 : kGroupPredict32);
+  return n >= from ? Form::group : Form::plain;
 }
 
-}  // namespace
+int64_t plain_elements(const Model& M, int precision, int64_t mc_min) {
+  int64_t end = 0;
+  auto range = [&](int c0, int c1) {
+    const int64_t n = M.cluster_start[c1 + 1] - M.cluster_start[c0];
+    if (n == 0) return;
+    const bool finer = M.fix_start[c1 + 1] > M.fix_start[c0];
+    if (launch_form(precision, M.N, mc_min, n, true, finer) == Form::plain ||
+        launch_form(precision, M.N, mc_min, n, false, finer) == Form::plain)
+      end = std::max(end, M.cluster_start[c1 + 1]);
+  };
+  for (int c = 0; c < M.C; ++c) {
+    range(c, c);
+    range(0, c);
+  }
+  return end;
+}
 
 hipError_t tuned_predict(const TunedData& t, int precision, int N, int c0, int c1, int64_t e0, int64_t e1,
                          const Sched& sc, hipStream_t s) {
+  if (e1 <= e0) return hipSuccess;
   const int64_t r0 = t.run_start[c0], nr = t.run_start[c1 + 1] - r0;
-  if (precision == 0) {
-    if (!group_order<double>(N)) return launch_predict_plain<double>(N, t.d64, e0, e1 - e0, sc, s);
-    const hipError_t st = launch_predict_group<double>(N, t.g64, e0, e1, sc, s);
-    return st == hipSuccess ? launch_finer<double>(N, t.g64, r0, nr, s) : st;
+  const Form form = launch_form(precision, N, t.mc_min, e1 - e0, true, t.finer[c1 + 1] > t.finer[c0]);
+  if (form == Form::group) {
+    hipError_t st = precision == 0 ? launch_predict_group<double>(N, t.g64, e0, e1, sc, s)
+                                   : launch_predict_group<float>(N, t.g32, e0, e1, sc, s);
+    if (st != hipSuccess) return st;
+    return precision == 0 ? launch_finer<double>(N, t.g64, r0, nr, s) : launch_finer<float>(N, t.g32, r0, nr, s);
   }
-  if (group_range(t, precision, e1 - e0)) {
-    const hipError_t st = launch_predict_group<float>(N, t.g32, e0, e1, sc, s);
-    return st == hipSuccess ? launch_finer<float>(N, t.g32, r0, nr, s) : st;
+  if (form == Form::plain) {
+    if (e1 > t.plain_end) return hipErrorInvalidValue;  // the flux matrices end there
+    return precision == 0 ? launch_predict_plain<double>(N, t.d64, e0, e1 - e0, sc, s)
+                          : launch_predict_plain<float>(N, t.d32, e0, e1 - e0, sc, s);
   }
-  if (e1 - e0 < t.mc_min) return launch_predict_plain<float>(N, t.d32, e0, e1 - e0, sc, s);
   hipError_t st = pred_dispatch_any(precision, N, t.pc, t.a, e0, e1, sc, s);
   if (st != hipSuccess) return st;
   return fixup_dispatch(N, t, t.fix_start[c0], t.fix_start[c1 + 1] - t.fix_start[c0], s);
@@ -492,11 +523,16 @@ hipError_t tuned_predict(const TunedData& t, int precision, int N, int c0, int c
 
 hipError_t tuned_correct(const TunedData& t, int precision, int N, int c0, int c1, int64_t e0, int64_t e1,
                          const Sched& sc, hipStream_t s) {
-  if (precision == 0)
-    return group_order<double>(N) ? launch_correct_group<double>(N, t.g64, e0, e1, sc, s)
-                                  : launch_correct_plain<double>(N, t.d64, e0, e1 - e0, sc, s);
-  if (group_range(t, precision, e1 - e0)) return launch_correct_group<float>(N, t.g32, e0, e1, sc, s);
-  if (e1 - e0 < t.mc_min) return launch_correct_plain<float>(N, t.d32, e0, e1 - e0, sc, s);
+  if (e1 <= e0) return hipSuccess;
+  const Form form = launch_form(precision, N, t.mc_min, e1 - e0, false, false);
+  if (form == Form::group)
+    return precision == 0 ? launch_correct_group<double>(N, t.g64, e0, e1, sc, s)
+                          : launch_correct_group<float>(N, t.g32, e0, e1, sc, s);
+  if (form == Form::plain) {
+    if (e1 > t.plain_end) return hipErrorInvalidValue;
+    return precision == 0 ? launch_correct_plain<double>(N, t.d64, e0, e1 - e0, sc, s)
+                          : launch_correct_plain<float>(N, t.d32, e0, e1 - e0, sc, s);
+  }
   // second-half traces into the inbox of the clusters on the second step of
   // their pair (h2_list is ordered by cluster): one launch per run of such
   // clusters

@@ -62,11 +62,21 @@ struct TunedData {
   std::vector<int64_t> fix_start, h2_start;  // per cluster: ranges of fix_elem and h2_list
   const int32_t* fix_elem = nullptr;         // [n + 1][2] first entry of fix_list of each element there, its dslot
   std::vector<int64_t> run_start;            // per cluster: ranges of the group arguments' fix_group
+  std::vector<int64_t> finer;                // per cluster: faces handing over to a finer neighbour, summed
+  int64_t plain_end = 0;     // no launch on the plain kernels reaches beyond this element
   GroupArgs<double> g64{};   // FP64
   GroupArgs<float> g32{};    // FP32 ranges below mc_min
   DevData<double> d64{};
   DevData<float> d32{};
 };
+
+// Kernels of a launch over n elements of a tuned handle (precision as in seis.h; finer: the
+// range has faces towards a finer neighbour): a work-group per element, a
+// work-group per 16 elements, a wavefront per 16 elements.
+enum class Form { plain, group, wave };
+Form launch_form(int precision, int N, int64_t mc_min, int64_t n, bool predictor, bool finer);
+// End of the elements that some launch (of a cluster, or of clusters 0..c) gives to the plain kernels.
+int64_t plain_elements(const Model& M, int precision, int64_t mc_min);
 
 // Matrix-core launches of one precision (tuned_f32.hip, tuned_bf16.hip).
 hipError_t pred_dispatch_f32(int N, const LaunchCfg& c, const TArgs& a, int64_t e0, int64_t e1, const Sched& sc,
@@ -85,9 +95,9 @@ hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevDat
                        const DevData<float>& d32, int tile, int acoustic, std::vector<void*>& owned,
                        int64_t& bytes);
 // Clusters c0..c1 = elements [e0, e1) (a launch may span several clusters;
-// sc gives each element's step parity). FP64 runs the group kernels (orders
-// 3..6, else the plain ones). A range of fewer than mc_min elements runs in FP32 on the
-// group or the plain kernels, a larger one on the matrix-core kernels, after which
+// sc gives each element's step parity). FP64, and in the 32-bit precisions a
+// range of fewer than mc_min elements, runs on the group or the plain kernels
+// (launch_form), a larger one on the matrix-core kernels, after which
 // faces handing over to a finer neighbour are rewritten with the first- and
 // second-half traces; before the matrix-core corrector the second-half traces
 // of the clusters on the second step of their pair are copied into the inbox of
