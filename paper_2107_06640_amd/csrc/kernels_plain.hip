@@ -52,11 +52,18 @@ struct alignas(4 * sizeof(T)) Triple {
   T v[4];
 };
 
-// acc[u][j] += sum_l m[u][l ld] row_l[j], l < n, of the triple at x. Eight modes
-// are requested together (four: 1.5% on that pass; sixteen in the one-item form: 15% slower)
-template <int GROUP, typename T>
+// Modes requested together: eight (four: 1.5% on that pass); twelve where that measured faster, in
+// the one-item form of orders 5 and 6, which only launches over few elements take (LTS box of 576
+// elements, a launch per cluster, a macro step in FP32: order 5 365 us with eight, 335 with twelve;
+// order 6 474 and 427; order 7 562 and 606), and at order 2, whose longest sum that is (152 and 142).
+template <int GROUP, int N>
+constexpr int kAhead = GROUP == 1 && (N == 1 || N == 4 || N == 5) ? 12 : 8;
+
+// acc[u][j] += sum_l m[u][l ld] row_l[j], l < n, of the triple at x
+template <int GROUP, int N, typename T>
 __device__ __forceinline__ void chain(T (&acc)[GROUP][3], const T* const (&m)[GROUP], int ld, const T* x, int n) {
-#pragma unroll 8
+  constexpr int U = kAhead<GROUP, N>;
+#pragma unroll U
   for (int l = 0; l < n; ++l) {
     const Triple<T> r = *reinterpret_cast<const Triple<T>*>(x + l * kPad);
 #pragma unroll
@@ -68,9 +75,10 @@ __device__ __forceinline__ void chain(T (&acc)[GROUP][3], const T* const (&m)[GR
   }
 }
 // the same, subtracted
-template <int GROUP, typename T>
+template <int GROUP, int N, typename T>
 __device__ __forceinline__ void chain_sub(T (&acc)[GROUP][3], const T* const (&m)[GROUP], int ld, const T* x, int n) {
-#pragma unroll 8
+  constexpr int U = kAhead<GROUP, N>;
+#pragma unroll U
   for (int l = 0; l < n; ++l) {
     const Triple<T> r = *reinterpret_cast<const Triple<T>*>(x + l * kPad);
 #pragma unroll
@@ -92,7 +100,7 @@ __device__ __forceinline__ void plain_level(const DevData<T>& d, const T* sD, T*
     const T* K[GROUP];
 #pragma unroll
     for (int u = 0; u < GROUP; ++u) K[u] = d.K + (size_t)(d0 + u) * B * B + m;
-    chain<GROUP, T>(acc, K, B, sD + pg * 4, nin);
+    chain<GROUP, N>(acc, K, B, sD + pg * 4, nin);
 #pragma unroll
     for (int u = 0; u < GROUP; ++u)
 #pragma unroll
@@ -112,7 +120,7 @@ __device__ __forceinline__ void plain_trace(const DevData<T>& d, int sets, const
     const T* E[GROUP];
 #pragma unroll
     for (int u = 0; u < GROUP; ++u) E[u] = d.Et + (size_t)(f0 + u) * B * Bf + m;
-    chain<GROUP, T>(acc, E, Bf, s + pg * 4, B);
+    chain<GROUP, N>(acc, E, Bf, s + pg * 4, B);
 #pragma unroll
     for (int u = 0; u < GROUP; ++u)
 #pragma unroll
@@ -135,16 +143,16 @@ __device__ __forceinline__ void plain_lift(const DevData<T>& d, int64_t e, const
       for (int dd = 0; dd < 3; ++dd) {
 #pragma unroll
         for (int u = 0; u < GROUP; ++u) M[u] = d.Kt + (size_t)dd * B * B + row[u];
-        chain<GROUP, T>(acc, M, B, sY + dd * B1 * kPad + pg * 4, B1);
+        chain<GROUP, N>(acc, M, B, sY + dd * B1 * kPad + pg * 4, B1);
       }
     }
     // the faces follow one another
 #pragma unroll
     for (int u = 0; u < GROUP; ++u) M[u] = d.Lt + row[u];
     if constexpr (VOLUME)
-      chain_sub<GROUP, T>(acc, M, B, sF + pg * 4, 4 * Bf);
+      chain_sub<GROUP, N>(acc, M, B, sF + pg * 4, 4 * Bf);
     else
-      chain<GROUP, T>(acc, M, B, sF + pg * 4, 4 * Bf);
+      chain<GROUP, N>(acc, M, B, sF + pg * 4, 4 * Bf);
 #pragma unroll
     for (int u = 0; u < GROUP; ++u) {
       if (k0 + u * H >= B) continue;
@@ -183,10 +191,10 @@ __global__ __launch_bounds__(NT_TALL) void k_predict_plain(DevData<T> d, int64_t
   if (tid < 3) sM[tid] = d.mat[e * 3 + tid];
   const int gs = d.dslot[e];
   T* gD = gs >= 0 ? d.gD + (int64_t)gs * (N + 1) * B * 9 : nullptr;
-  // the half-step integral, for a face towards a finer neighbour (four loads in flight
-  // together: || would chain them)
-  const int8_t* md4 = d.mode + e * 4;
-  const bool finer = (md4[0] == 2) | (md4[1] == 2) | (md4[2] == 2) | (md4[3] == 2);
+  // the half-step integral, for a face towards a finer neighbour: one of the four modes (bytes, 0..3)
+  // is 2. One load: four behind || follow one another.
+  const unsigned md4 = *reinterpret_cast<const unsigned*>(d.mode + e * 4);
+  const bool finer = (md4 & ~(md4 << 1) & 0x02020202u) != 0;
   for (int i = tid; i < B * 9; i += NT) {
     const T q = d.Q[qidx(e, i / 9, i % 9, RT)];
     const int x = padded(i / 9, i % 9);
@@ -228,10 +236,15 @@ __global__ __launch_bounds__(NT_TALL) void k_predict_plain(DevData<T> d, int64_t
     __syncthreads();
   }
   // traces at the face nodes: full step and first half step
-  if (single)
+  if constexpr (kOneItem<N>) {
     plain_trace<1, T, N>(d, finer ? 2 : 1, sI, sV, sIh, sVh);
-  else
-    plain_trace<2, T, N>(d, finer ? 2 : 1, sI, sV, sIh, sVh);
+  } else {  // one set fills the threads
+    if (single)
+      plain_trace<1, T, N>(d, 1, sI, sV, sI, sV);
+    else
+      plain_trace<2, T, N>(d, 1, sI, sV, sI, sV);
+    if (finer) plain_trace<2, T, N>(d, 1, sIh, sVh, sIh, sVh);
+  }
   __syncthreads();
   // hand the traces to the neighbours (in their node numbering)
   for (int i = tid; i < 4 * Bf * 9; i += NT) {
