@@ -217,22 +217,80 @@ hipError_t corr_dispatch_any(int precision, int N, const LaunchCfg& c, const TAr
   return corr_dispatch_bf16(N, c, a, e0, e1, s);
 }
 
-// Half-step hand-over: the groups with a face towards a finer neighbour (slot in
-// Ih) and, per cluster, their runs of the model's fix_list (sorted by element).
+// A launch of the wavefront form (mc_min) needs elements enough to fill the chip with a
+// wavefront per 16; a smaller one takes a work-group per 16 elements (group) where that keeps more
+// of the chip busy than a work-group per element (plain). Measured, us of one launch, plain - group:
+//   corrector, from 256 elements on: FP32 288 elements 0.9 (order 3) .. 3.5 (order 6), 1920 2.8 .. 12; FP64
+//     288 -0.3 .. 0.5, 1920 3 .. 22; 162 elements 0.2 .. -0.2 and -0.4 .. -5;
+//   predictor, FP32 from 256 on: 162 elements -0.3 (order 3) .. -27 (order 7), 288 0.2, -0.4, 2.9, -0.8, -3.9
+//     (orders 3..7), 720 0.6 .. 4.1, 1920 2.5 .. 67;
+//   predictor, FP64 from 896 on: 720 elements -1.1 .. -3.8, 900 -0.5, -1.8, 0.2, 6.6 (orders 3..6), 1080 0.2 .. 35;
+//   predictor with faces towards a finer neighbour, whose traces take a launch of their own, from
+//     1536 on: LTS boxes of 576, 900, 1296 elements -4 .. -33, 1903 -4 .. 32, 2304 -0.4 .. 72.
+// Small ranges of the BF16 precisions stay on the plain kernels: BF16 rounding amplifies another
+// order of the FP32 sums (one ulp in a few elements of a small cluster becomes 3e-4 of the
+// result in four steps).
+namespace {
+constexpr int64_t kGroupCorrect = 256, kGroupPredict32 = 256, kGroupPredict64 = 896, kGroupFiner = 1536;
+}  // namespace
+
+Form launch_form(int precision, int N, int64_t mc_min, int64_t n, bool predictor, bool finer) {
+  if (precision != 0 && n >= mc_min) return Form::wave;
+  if (precision > 1 || (precision == 0 && !group_order<double>(N))) return Form::plain;
+  int64_t from = kGroupCorrect;
+  if (predictor) from = finer ? kGroupFiner : (precision == 0 ? kGroupPredict64 : kGroupPredict32);
+  return n >= from ? Form::group : Form::plain;
+}
+
+namespace {
+
+// f(c0, c1) of every element range that a launch may cover: a cluster, or clusters 0..c
+template <class F>
+void launch_ranges(const Model& M, F f) {
+  for (int c = 0; c < M.C; ++c) {
+    if (M.cluster_start[c + 1] > M.cluster_start[c]) f(c, c);
+    if (c > 0 && M.cluster_start[c + 1] > 0) f(0, c);
+  }
+}
+
+Form range_form(const Model& M, int precision, int64_t mc_min, int c0, int c1, bool predictor) {
+  return launch_form(precision, M.N, mc_min, M.cluster_start[c1 + 1] - M.cluster_start[c0], predictor,
+                     M.fix_start[c1 + 1] > M.fix_start[c0]);
+}
+
+}  // namespace
+
+int64_t plain_elements(const Model& M, int precision, int64_t mc_min) {
+  int64_t end = 0;
+  launch_ranges(M, [&](int c0, int c1) {
+    for (bool predictor : {true, false})
+      if (range_form(M, precision, mc_min, c0, c1, predictor) == Form::plain) end = std::max(end, M.cluster_start[c1 + 1]);
+  });
+  return end;
+}
+
+// Half-step hand-over of the clusters that some launch predicts on the group kernels: the
+// groups with a face towards a finer neighbour (slot in Ih) and, per cluster, their runs of the
+// model's fix_list (sorted by element).
 struct FinerLists {
   std::vector<int32_t> hslot, runs;
   std::vector<int64_t> start;
   int32_t slots = 0;
 };
 
-FinerLists finer_lists(const Model& M) {
+FinerLists finer_lists(const Model& M, int precision, int64_t mc_min) {
+  std::vector<char> grouped(M.C, 0);
+  launch_ranges(M, [&](int c0, int c1) {
+    if (range_form(M, precision, mc_min, c0, c1, true) == Form::group)
+      for (int c = c0; c <= c1; ++c) grouped[c] = 1;
+  });
   FinerLists r;
   r.hslot.assign((M.E + 15) / 16, -1);
   r.start.assign(M.C + 1, 0);
   for (int c = 0; c < M.C; ++c) {
     r.start[c] = (int64_t)r.runs.size() / 3;
     int32_t last = -1;
-    for (int64_t i = M.fix_start[c]; i < M.fix_start[c + 1]; ++i) {
+    for (int64_t i = M.fix_start[c]; grouped[c] && i < M.fix_start[c + 1]; ++i) {
       const int32_t grp = M.fix_list[i] >> 6;  // entries are element * 4 + face
       if (r.hslot[grp] < 0) r.hslot[grp] = r.slots++;
       if (grp != last) {
@@ -271,7 +329,7 @@ hipError_t group_build(GroupArgs<T>& a, TunedData& t, const Model& M, const DevD
   a.tgt = d.tgt;
   a.half2 = d.half2;
   a.rhalf2 = d.rhalf2;
-  const FinerLists fl = finer_lists(M);
+  const FinerLists fl = finer_lists(M, t.precision, t.mc_min);
   t.run_start = fl.start;
   // a group hands over from its slot of I~_h: derivatives only for gravity and fault faces
   std::vector<int32_t> mh(M.E, 0), ds(M.gslot.begin(), M.gslot.end());
@@ -325,13 +383,18 @@ hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevDat
     t.fixed = 1;
   }
   t.run_start.assign(M.C + 1, 0);
+  bool grouped = false;  // whether some launch takes the group kernels
+  launch_ranges(M, [&](int c0, int c1) {
+    for (bool predictor : {true, false})
+      grouped = grouped || range_form(M, precision, t.mc_min, c0, c1, predictor) == Form::group;
+  });
   if (precision == 0) {
-    const hipError_t sg = group_order<double>(M.N) ? group_build(t.g64, t, M, d64, owned, bytes) : hipSuccess;
+    const hipError_t sg = grouped ? group_build(t.g64, t, M, d64, owned, bytes) : hipSuccess;
     t.ready = sg == hipSuccess;
     return sg;
   }
   hipError_t st = hipSuccess;
-  if (precision == 1) st = group_build(t.g32, t, M, d32, owned, bytes);
+  if (grouped) st = group_build(t.g32, t, M, d32, owned, bytes);
   if (st != hipSuccess) return st;
   TArgs& a = t.a;
   a.Q = d32.Q;
@@ -456,48 +519,6 @@ hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevDat
   if (st != hipSuccess) return st;
   t.ready = 1;
   return hipSuccess;
-}
-
-// A launch of the wavefront form (mc_min) needs elements enough to fill the chip with a
-// wavefront per 16; a smaller one takes a work-group per 16 elements (group) where that keeps more
-// of the chip busy than a work-group per element (plain). Measured, us of one launch, plain - group:
-//   corrector, from 256 elements on: FP32 288 elements 0.9 (order 3) .. 3.5 (order 6), 1920 2.8 .. 12; FP64
-//     288 -0.3 .. 0.5, 1920 3 .. 22; 162 elements 0.2 .. -0.2 and -0.4 .. -5;
-//   predictor, FP32 from 256 on: 162 elements -0.3 (order 3) .. -27 (order 7), 288 0.2, -0.4, 2.9, -0.8, -3.9
-//     (orders 3..7), 720 0.6 .. 4.1, 1920 2.5 .. 67;
-//   predictor, FP64 from 896 on: 720 elements -1.1 .. -3.8, 900 -0.5, -1.8, 0.2, 6.6 (orders 3..6), 1080 0.2 .. 35;
-//   predictor with faces towards a finer neighbour, whose traces take a launch of their own, from
-//     1536 on: LTS boxes of 576, 900, 1296 elements -4 .. -33, 1903 -4 .. 32, 2304 -0.4 .. 72.
-// Small ranges of the BF16 precisions stay on the plain kernels: BF16 rounding amplifies another
-// order of the FP32 sums (one ulp in a few elements of a small cluster becomes 3e-4 of the
-// result in four steps).
-namespace {
-constexpr int64_t kGroupCorrect = 256, kGroupPredict32 = 256, kGroupPredict64 = 896, kGroupFiner = 1536;
-}  // namespace
-
-Form launch_form(int precision, int N, int64_t mc_min, int64_t n, bool predictor, bool finer) {
-  if (precision != 0 && n >= mc_min) return Form::wave;
-  if (precision > 1 || (precision == 0 && !group_order<double>(N))) return Form::plain;
-  int64_t from = kGroupCorrect;
-  if (predictor) from = finer ? kGroupFiner : (precision == 0 ? kGroupPredict64 : kGroupPredict32);
-  return n >= from ? Form::group : Form::plain;
-}
-
-int64_t plain_elements(const Model& M, int precision, int64_t mc_min) {
-  int64_t end = 0;
-  auto range = [&](int c0, int c1) {
-    const int64_t n = M.cluster_start[c1 + 1] - M.cluster_start[c0];
-    if (n == 0) return;
-    const bool finer = M.fix_start[c1 + 1] > M.fix_start[c0];
-    if (launch_form(precision, M.N, mc_min, n, true, finer) == Form::plain ||
-        launch_form(precision, M.N, mc_min, n, false, finer) == Form::plain)
-      end = std::max(end, M.cluster_start[c1 + 1]);
-  };
-  for (int c = 0; c < M.C; ++c) {
-    range(c, c);
-    range(0, c);
-  }
-  return end;
 }
 
 hipError_t tuned_predict(const TunedData& t, int precision, int N, int c0, int c1, int64_t e0, int64_t e1,
