@@ -107,10 +107,10 @@ typedef struct {
   int max_clusters; /* rate-2 LTS clusters (Sec. 4.4); 1 = global time stepping */
   void *stream;     /* hipStream_t to launch on; NULL = the default stream */
   int tile;         /* elements per work-group for the tuned kernels (32: 2 wavefronts, 64: 4);
-                       0 = autotuned: at set-up the launch configurations and the predictor's
-                       shape (FP32: I~ parked in LDS or in HBM; BF16: 16x16x16 or 16x16x32
-                       matrix-core products) are timed on the largest cluster and the fastest
-                       kept, cached per (kernel sources, device, order, precision, size class)
+                       0 = autotuned: at set-up the launch configurations and, in FP32, the
+                       predictor's shape (I~ parked in LDS or in HBM) are timed on the largest
+                       cluster and the fastest kept, cached per (kernel sources, device, order,
+                       precision, size class)
                        in the file $SEIS_TUNE_CACHE (default $HOME/.cache/seis/tune.txt).
                        SEIS_TUNE=0 in the environment disables tuning;
                        SEIS_TUNE=w,cap,remap,w,cap,remap[,split[,shape]] fixes it. */
@@ -162,7 +162,8 @@ typedef struct {
                            2 read from the tuning cache */
   int fused;            /* options.fused */
   int shape;            /* the predictor's shape: FP32 0 = I~ parked in LDS as far as it fits,
-                           1 = in HBM; BF16 0 = 16x16x16 products, 1 = 16x16x32 products */
+                           1 = in HBM; BF16 0 = 16x16x16 products, 1 = 16x16x32 products (by the
+                           order, tuned or not, unless SEIS_TUNE names a shape) */
   int64_t n_acoustic_groups; /* 16-element groups run in the 4-quantity form (options.acoustic) */
   int64_t n_fault_faces; /* SEIS_FACE_FAULT faces, each counted once (seis_set_fault) */
 } seis_info_t;

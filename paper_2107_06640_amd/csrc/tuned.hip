@@ -382,6 +382,10 @@ hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevDat
     t.cc = LaunchCfg{w, 0, 0, 2};
     t.fixed = 1;
   }
+  // The two product shapes of BF16 round differently, so the shape follows from the order, tuned
+  // or not, and not from a timing (which chose the same in all but a few runs): 32 K entries
+  // at a time where no product is half empty. SEIS_TUNE alone overrides it.
+  if (precision == 2) t.pc.variant = row_tiles(n_basis(M.N)) % 2 == 0;
   t.run_start.assign(M.C + 1, 0);
   bool grouped = false;  // whether some launch takes the group kernels
   launch_ranges(M, [&](int c0, int c1) {
@@ -581,8 +585,8 @@ namespace {
 // order, precision, size class) in a text cache, one line per key:
 //   <key> <waves> <cap> <remap> <waves> <cap> <remap> <split> <variant>
 // (predictor, corrector, the corrector's passes over its output rows, the
-// predictor's shape: FP32 LDS or HBM park of I~, BF16 16x16x16 or 16x16x32
-// products). The cache is $SEIS_TUNE_CACHE, else $HOME/.cache/seis/tune.txt.
+// predictor's shape: FP32 LDS or HBM park of I~, timed; BF16 16x16x16 or 16x16x32
+// products, by the order). The cache is $SEIS_TUNE_CACHE, else $HOME/.cache/seis/tune.txt.
 // SEIS_TUNE=0 disables tuning; SEIS_TUNE=w,cap,remap,w,cap,remap[,split[,variant]]
 // fixes the configuration.
 
@@ -710,13 +714,9 @@ hipError_t tuned_autotune(TunedData& t, const Model& M, hipStream_t s) {
       for (int rm : {0, 1}) {
         const LaunchCfg c{w, cap, rm, 2, 0};
         float ms = 0.0f;
-        // predictor: both shapes of FP32; split BF16 has one, and the two of BF16
-        // round differently, so theirs follows from the order and not from a
-        // timing (which chose the same in all but a few runs): 32 K entries at a
-        // time where no product is half empty
-        const int rt = row_tiles(n_basis(t.N));
-        const int v0 = t.precision == 2 && rt % 2 == 0, v1 = t.precision == 1 ? 1 : v0;
-        for (int var = v0; var <= v1 && cap <= 2; ++var) {
+        // predictor: both shapes of FP32, the one that set-up chose in BF16
+        for (int var : {0, 1}) {
+          if (cap > 2 || (t.precision != 1 && var != t.pc.variant)) continue;
           LaunchCfg cv = c;
           cv.variant = var;
           hipError_t st = time_launch(
