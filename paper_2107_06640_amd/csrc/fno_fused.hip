@@ -31,6 +31,7 @@
 #include <cstdint>
 
 #include "../../include/fno.h"
+#include "lds_limit.hpp"
 
 namespace {
 
@@ -1000,14 +1001,10 @@ unsigned blocks(int64_t tasks, int per_cu) {
 
 int done() { return hipGetLastError() == hipSuccess ? 0 : -3; }
 
-// launch with lds bytes of dynamic LDS (beyond the default 64 KB the kernel's limit is raised to a whole CU's, once)
+// launch with lds bytes of dynamic LDS
 template <auto K, class... A>
 int launch(unsigned grid, int threads, int lds, void* stream, A... args) {
-  if (lds > 64 * 1024) {
-    static const hipError_t limit =
-        hipFuncSetAttribute((const void*)K, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-    if (limit != hipSuccess) return -3;
-  }
+  if (lds > 64 * 1024 && seis::raise_lds_limit<K>(kLds) != hipSuccess) return -3;
   hipLaunchKernelGGL(K, dim3(grid), dim3(threads), lds, (hipStream_t)stream, args...);
   return done();
 }

@@ -21,6 +21,7 @@
 
 #include "elastic.hpp"
 #include "layout.hpp"
+#include "lds_limit.hpp"
 
 namespace seis {
 
@@ -631,9 +632,8 @@ __global__ __launch_bounds__(kFinerThreads) void k_finer_group(GroupArgs<T> a, i
 template <auto K, class... A>
 hipError_t launch(unsigned grid, int threads, int lds, hipStream_t s, A... args) {
   if (lds > 64 * 1024) {
-    static const hipError_t limit =
-        hipFuncSetAttribute((const void*)K, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (limit != hipSuccess) return limit;
+    const hipError_t st = raise_lds_limit<K>(160 * 1024);
+    if (st != hipSuccess) return st;
   }
   hipLaunchKernelGGL(K, dim3(grid), dim3(threads), lds, s, args...);
   return hipGetLastError();

@@ -43,6 +43,7 @@
 
 #include "elastic.hpp"
 #include "layout.hpp"
+#include "lds_limit.hpp"
 #include "tuned.hpp"
 
 #ifndef SEIS_SOURCE_HASH
@@ -1377,12 +1378,6 @@ unsigned grid_size(int64_t ngroups, int W, int cap) {
   return (unsigned)std::min<int64_t>(full, (int64_t)num_cus() * cap);
 }
 
-template <class KernelPtr>
-hipError_t prep(KernelPtr k, int lds) {
-  return hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-}
-
-
 template <class Op, int N, int W>
 hipError_t launch_pred(const TArgs& a, int64_t e0, int64_t e1, const Sched& sc, const LaunchCfg& c, hipStream_t s) {
   if (e1 <= e0) return hipSuccess;
@@ -1391,7 +1386,7 @@ hipError_t launch_pred(const TArgs& a, int64_t e0, int64_t e1, const Sched& sc, 
   const unsigned grid = grid_size(ng, W, c.cap);
   constexpr int lds = PredLds<Op, N, W>::bytes;
   static_assert(lds <= 160 * 1024, "predictor LDS exceeds the 160 KB of a CU");
-  static hipError_t attr = prep(k_predict_tuned<Op, N, W>, lds);
+  const hipError_t attr = raise_lds_limit<k_predict_tuned<Op, N, W>>(lds);
   if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL((k_predict_tuned<Op, N, W>), dim3(grid), dim3(64 * W), lds, s, a, e0, e1, sc, c.remap);
   return hipGetLastError();
@@ -1403,7 +1398,7 @@ hipError_t launch_corr(const TArgs& a, int64_t e0, int64_t e1, const LaunchCfg& 
   using L = Lay<Op, N>;
   const int64_t ng = ((e1 - 1) >> 4) - (e0 >> 4) + 1;
   const unsigned grid = grid_size(ng, W, c.cap);
-  static hipError_t attr = prep(k_correct_tuned<Op, N, W, SPLIT>, L::lift_bytes);
+  const hipError_t attr = raise_lds_limit<k_correct_tuned<Op, N, W, SPLIT>>(L::lift_bytes);
   if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL((k_correct_tuned<Op, N, W, SPLIT>), dim3(grid), dim3(64 * W), L::lift_bytes, s, a, e0, e1,
                      c.remap);
