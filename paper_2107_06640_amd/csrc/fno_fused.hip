@@ -71,6 +71,17 @@ __device__ __forceinline__ float gelu_d(float x) {
   return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * 0.39894228040143268f * expf(-0.5f * x * x);
 }
 
+// Mask of a fragment's eight K entries 8g.. of the last 32, of which n are real: the others
+// meet zeros, but 0 x inf would not be zero where an activation is infinite.
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u4 last_mask(int n, int g) {
+  u4 m;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) m[j] = (8 * g + 2 * j < n ? 0xffffu : 0u) | (8 * g + 2 * j + 1 < n ? 0xffff0000u : 0u);
+  return m;
+}
+__device__ __forceinline__ bf8 masked(bf8 x, u4 m) { return __builtin_bit_cast(bf8, __builtin_bit_cast(u4, x) & m); }
+
 // four consecutive values from i on, zero from n on; V4: p is 16-byte aligned and n a multiple of 4
 template <bool V4>
 __device__ __forceinline__ f4 load4(const float* p, int64_t i, int64_t n) {
@@ -209,6 +220,7 @@ __global__ __launch_bounds__(256) void k_head(int64_t n, int W, int H, const flo
     a2[k] = pack8(x);
   }
   const float b2 = q2[0];
+  const u4 last = last_mask(H - 32 * (chunks - 1), g);
   const int64_t tiles = (n + 63) / 64;
   int buf = 0;
   for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x, buf ^= 1) {
@@ -237,7 +249,11 @@ __global__ __launch_bounds__(256) void k_head(int64_t n, int W, int H, const flo
     f4 acc = zero4();
 #pragma unroll
     for (int k = 0; k < 4 * HC; ++k)
-      if (k < chunks) acc = mfma(a2[k], lds8(G + (16 * w + c) * LD + 32 * k + 8 * g), acc);
+      if (k < chunks) {
+        bf8 x = lds8(G + (16 * w + c) * LD + 32 * k + 8 * g);
+        if (k == chunks - 1) x = masked(x, last);
+        acc = mfma(a2[k], x, acc);
+      }
     const int64_t p = p0 + 16 * w + c;
     if (g == 0 && p < n) y[p] = acc[0] + b2;
   }
@@ -260,6 +276,7 @@ __global__ __launch_bounds__(256, KC * HC == 1 ? 2 : 1) void k_head_bwd(int64_t 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, c = lane & 15;
   const int chunks = (H + 31) / 32;
   stage(sQ, Q1, 1, W, W, H, 32 * KC, 128 * HC, LD, tid, 256);
+  const u4 last = last_mask(H - 32 * (chunks - 1), g);
   bf8 a1[HC][2][KC];
   float b1[HC][2][4], q2b[HC][2][4], s1[HC][2][4], s2[HC][2][4];
   f4 dw[HC][2][WT];
@@ -353,8 +370,10 @@ __global__ __launch_bounds__(256, KC * HC == 1 ? 2 : 1) void k_head_bwd(int64_t 
 #pragma unroll
     for (int mt = 0; mt < WT; ++mt) {
       f4 acc = zero4();
-      for (int k = 0; k < chunks; ++k)
+      for (int k = 0; k < chunks - 1; ++k)
         acc = mfma(lds8(sQ + (16 * mt + c) * LD + 32 * k + 8 * g), lds8(sD + (16 * w + c) * LD + 32 * k + 8 * g), acc);
+      const int k = 32 * (chunks - 1) + 8 * g;
+      acc = mfma(lds8(sQ + (16 * mt + c) * LD + k), masked(lds8(sD + (16 * w + c) * LD + k), last), acc);
 #pragma unroll
       for (int r = 0; r < 4; ++r)
         if (16 * mt + 4 * g + r < W && q < n) dv[(int64_t)(16 * mt + 4 * g + r) * n + q] = acc[r];
