@@ -498,9 +498,9 @@ class CountingKernels(Kernels):
         self._add(slices * (Y * 2 * m * T + 2 * 4 * m * m * Y), slices * (Y * T + 4 * m * m))
         super().dft_ty(slices, Y, T, m, *args)
 
-    def dft_x(self, batch, M, K, inner, *args):
-        self._add(batch * 2 * M * K * inner, 3 * batch * max(M, K) * inner)
-        super().dft_x(batch, M, K, inner, *args)
+    def dft_x(self, batch, M, K, inner, inverse, *args):
+        self._add(batch * 2 * M * K * inner, batch * inner * (K + 2 * M if inverse else 2 * K + M))
+        super().dft_x(batch, M, K, inner, inverse, *args)
 
     def mix(self, B, W, nm, *args):
         self._add(4 * nm * B * W * W, nm * (4 * B * W + 2 * W * W))
@@ -511,8 +511,9 @@ class CountingKernels(Kernels):
         super().mix_grad(B, W, nm, *args)
 
     def idft_yt(self, B, X, Y, T, m, W, *args):
-        n = B * X * Y * T
-        self._add(n * W * (W + 2 * m) + B * X * W * Y * 2 * m * 4 * m, W * (3 * n + B * X * 4 * m * m))
+        n, (z, a) = B * X * Y * T, args[-3:-1]
+        written = (z is not None) + (a is not None)
+        self._add(n * W * (W + 2 * m) + B * X * W * Y * 2 * m * 4 * m, W * ((1 + written) * n + B * X * 4 * m * m))
         super().idft_yt(B, X, Y, T, m, W, *args)
 
 
