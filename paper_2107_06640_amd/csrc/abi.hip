@@ -167,7 +167,7 @@ int build_dev(seis_t* h, DevData<T>& d) {
   const int B = M.B, Bf = M.Bf, N = M.N;
   d.E = E;
   d.g = M.g;
-  T *Q, *G, *mat, *Fm, *Fp, *In, *H2, *gD, *K, *Ef, *Kt, *Et, *Lt;
+  T *Q, *G, *mat, *Fm, *Fp, *In, *H2, *gD, *K, *Kt, *Et, *Lt;
   const int RT = row_tiles(B), FT = row_tiles(Bf);
   HIPCHK(h, b.alloc(&Q, q_size(E, RT)), "alloc Q");
   HIPCHK(h, hipMemset(Q, 0, q_size(E, RT) * sizeof(T)), "memset Q");
@@ -184,12 +184,11 @@ int build_dev(seis_t* h, DevData<T>& d) {
   const int64_t Fg = (int64_t)M.g_elem.size();
   HIPCHK(h, b.alloc(&gD, std::max<int64_t>(std::max<int64_t>(Fg, M.n_dslot), 1) * (N + 1) * B * 9), "alloc gD");
   HIPCHK(h, upload(b, &K, M.ref.K), "upload K");
-  HIPCHK(h, upload(b, &Ef, M.ref.E), "upload E");
   HIPCHK(h, upload(b, &Kt, transposed(M.ref.K, 3, B, B)), "upload K transposed");
   HIPCHK(h, upload(b, &Et, transposed(M.ref.E, 4, Bf, B)), "upload E transposed");
   HIPCHK(h, upload(b, &Lt, transposed(M.ref.L, 4, B, Bf)), "upload L");
   d.Q = Q; d.G = G; d.mat = mat; d.Fm = Fm; d.Fp = Fp; d.In = In; d.H2 = H2; d.gD = gD;
-  d.K = K; d.Ef = Ef; d.Kt = Kt; d.Et = Et; d.Lt = Lt;
+  d.K = K; d.Kt = Kt; d.Et = Et; d.Lt = Lt;
   return SEIS_OK;
 }
 

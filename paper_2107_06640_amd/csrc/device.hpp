@@ -4,7 +4,8 @@
 //   Q     [E][B][9]        modal coefficients (compute type)
 //   G     [E][9]           dt_c * dxi_d/dx_e (row d)          -- scaled star matrices are
 //   mat   [E][3]           lambda, mu, 1/rho                     rebuilt from these on the fly
-//   Fm,Fp [E][4][81]       2 A_i dt_c / |J| * F-+ (row p, column r)
+//   Fm,Fp [E][4][81]       2 A_i dt_c / |J| * F-+ (row p, column r), of the leading
+//                          elements that some launch gives to the plain kernels
 //   In    [E][4][Bf][9]    time-integrated neighbour traces received at face nodes,
 //                          divided by the receiver's dt (its own node numbering)
 //   H2    [n_half2][Bf][9] second-half traces from a coarser neighbour
@@ -56,7 +57,6 @@ struct DevData {
   T* gD;
   // reference matrices (compute type)
   const T* K;   // [3][B][B]
-  const T* Ef;  // [4][Bf][B]
   const T* Kt;  // [3][B][B] K^d transposed
   const T* Et;  // [4][B][Bf] face traces, node-contiguous
   const T* Lt;  // [4][Bf][B] lifts, row-contiguous

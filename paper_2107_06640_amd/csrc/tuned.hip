@@ -408,7 +408,6 @@ hipError_t tuned_build(TunedData& t, const Model& M, int precision, const DevDat
   a.tgt = d32.tgt;
   a.mode = d32.mode;
   a.hperm = d32.hperm;
-  a.Ef = d32.Ef;
   a.H2 = d32.H2;
   a.half2 = d32.half2;
   a.rhalf2 = d32.rhalf2;

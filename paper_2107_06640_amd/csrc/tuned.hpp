@@ -26,7 +26,6 @@ struct TArgs {
   const int32_t* pinv;  // [6][Bf]
   const int32_t* dslot; // [E] slot of the stored time derivatives, -1 none
   float* gD;            // [slots][N+1][B][9] time derivatives (gravity faces, then hand-over to finer neighbours)
-  const float* Ef;      // [4][Bf][B] face-trace matrices (FP32)
   float* H2;            // [n_half2][Bf][9] second-half traces for finer neighbours
   const int32_t* half2; // [E][4] writer: second-half slot, -1 none
   const int32_t* rhalf2;// [E][4] reader: second-half slot, -1 none
