@@ -190,7 +190,11 @@ int seis_setup(const seis_mesh_t *mesh, const seis_materials_t *mat, int order,
 
 /* Copy state from host FP64: dofs [E][B][9] (caller order) and/or eta
  * [F_g][(N+1)^2]; either may be NULL to keep the current value. Resets the
- * schedule to the start of a macro step and the simulated time to 0. */
+ * schedule to the start of a macro step and the simulated time to 0. The DOFs
+ * go through pinned memory that the handle allocates at its first transfer (2 MiB
+ * for each of two buffers of up to eight threads, less for a small state) and
+ * keeps until seis_destroy; up to eight threads, ended before the call
+ * returns, share the copies. SEIS_EDEVICE if the pinned memory is refused. */
 int seis_write(seis_t *h, const double *dofs, const double *eta);
 
 /* Uplift history driving the SEIS_FACE_VELOCITY faces (a seafloor uplift,
@@ -276,6 +280,7 @@ int seis_run(seis_t *h, int n);
 
 /* Copy state to host FP64 (synchronises the stream first): dofs [E][B][9]
  * in caller element order and/or eta [F_g][(N+1)^2]; either may be NULL.
+ * The DOFs go through the pinned memory and threads of seis_write.
  * Errors: SEIS_EORDER if a cluster is between predict and correct. */
 int seis_read(seis_t *h, double *dofs, double *eta);
 

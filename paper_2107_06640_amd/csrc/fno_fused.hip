@@ -10,9 +10,11 @@
 // network). Only the weight gradients, sums over all points that nothing
 // rounds again, are summed in another order.
 //
-// Every stage is bound by reading and writing its activations. Measured on 64 samples of a
-// 64 x 64 x 32 grid, width 32, 12 modes, hidden width 128 (an activation is 1.07 GB; a large
-// copy moves 4.9 TB/s), average per call in a training step: k_idft_yt 854 us (two or
+// The stages over the grid move little but their activations, at half to three quarters of the
+// rate of a large copy (4.9 TB/s); what keeps them below it is the latency of a work-group's phases
+// (loads, products, exchange through LDS, stores). The projection is bound by the erf and exp of
+// GELU. Measured on 64 samples of a 64 x 64 x 32 grid, width 32, 12 modes, hidden width 128 (an
+// activation is 1.07 GB), average per call in a training step: k_idft_yt 854 us (two or
 // three activations, 2.5-3.8 TB/s), k_layer_bwd 1039 (three, 3.1), k_dft_ty 315 (one,
 // 3.4), k_dft_x 100, k_mix 108, k_mix_grad 94, k_pointwise 273, k_head 575 and k_head_bwd
 // 1944 (GELU and its derivative of 128 hidden values a point). The step takes 18.8 ms, with the general

@@ -7,7 +7,8 @@
 // room for FP64 (the matrix cores' v_mfma_f64_16x16x4), and finishes a small
 // range in a fraction of the time. It is the FP64 form of the tuned kernels
 // at orders 3..6 (the rows of order 7 exceed LDS) and the form of FP32 ranges
-// of 256 to options.mc_min elements (orders 3..7).
+// below options.mc_min elements (orders 3..7); the smallest ranges of both take
+// the plain kernels (launch_form in tuned.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -20,10 +20,10 @@ namespace seis {
 namespace {
 
 // Threads per element: 128 for throughput, as many as the longest loops have
-// items, so that more work-groups share a CU (a pass of BF16 steps whose finest cluster of 1971
-// elements runs here took 8.76 ms; 192 and 256 threads 9.05, 512 10.0); a launch
+// items, so that more work-groups share a CU (a pass of BF16 steps at order 6 whose finest cluster of
+// 1971 elements runs here took 8.76 ms; 192 and 256 threads 9.05, 512 10.0); a launch
 // over a few elements (a tiny LTS cluster) is bound by the latency of one
-// work-group, so it uses 1024.
+// work-group, so it uses 1024, or 256 at the lowest orders (threads_for).
 // The thread count is a launch parameter of one compiled kernel, not a
 // template argument, so that an element's arithmetic (and its rounding) is
 // the same whichever launch covers it.
@@ -382,6 +382,7 @@ __global__ __launch_bounds__(256) void k_gravity(DevData<T> d, const int32_t* gl
       em = sStep[m] * (fm - a * em);
       eta1 += em;
       // em dt / (m + 2), correctly rounded: the quotient by the reciprocal, corrected by its remainder
+      // (Markstein's division)
       const double x = em * dt, r = sInv[m], y = x * r;
       H += isfinite(y) ? fma(fma(-y, double(m + 2), x), r, y) : y;
     }
