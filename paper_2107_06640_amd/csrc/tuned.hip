@@ -705,39 +705,57 @@ hipError_t tuned_autotune(TunedData& t, const Model& M, hipStream_t s) {
       return hipSuccess;
     }
   }
-  const int reps = 2;
-  LaunchCfg bp = t.pc, bc = t.cc;
-  float tp = 1e30f, tc = 1e30f;
+  struct Timed {
+    LaunchCfg c;
+    float ms;
+  };
+  auto predict = [&](const LaunchCfg& c, int reps, float& ms) {
+    return time_launch([&]() { return pred_dispatch_any(t.precision, t.N, c, t.a, e0, ei, Sched{}, s); }, s, reps, ms);
+  };
+  auto correct = [&](const LaunchCfg& c, int reps, float& ms) {
+    return time_launch([&]() { return corr_dispatch_any(t.precision, t.N, c, t.a, e0, ei, s); }, s, reps, ms);
+  };
+  std::vector<Timed> pred, corr;
   for (int w : {4, 2})
     for (int cap : {0, 1, 2, 4})
       for (int rm : {0, 1}) {
-        const LaunchCfg c{w, cap, rm, 2, 0};
+        LaunchCfg c{w, cap, rm, 2, 0};
         float ms = 0.0f;
         // predictor: both shapes of FP32, the one that set-up chose in BF16
         for (int var : {0, 1}) {
           if (cap > 2 || (t.precision != 1 && var != t.pc.variant)) continue;
-          LaunchCfg cv = c;
-          cv.variant = var;
-          hipError_t st = time_launch(
-              [&]() { return pred_dispatch_any(t.precision, t.N, cv, t.a, e0, ei, Sched{}, s); }, s, reps, ms);
+          c.variant = var;
+          const hipError_t st = predict(c, 2, ms);
           if (st != hipSuccess) return st;
-          if (ms < tp) {
-            tp = ms;
-            bp = cv;
-          }
+          pred.push_back({c, ms});
         }
+        c.variant = 0;
         for (int sp : {2, 1}) {
-          LaunchCfg cs = c;
-          cs.split = sp;
-          hipError_t st = time_launch(
-              [&]() { return corr_dispatch_any(t.precision, t.N, cs, t.a, e0, ei, s); }, s, reps, ms);
+          c.split = sp;
+          const hipError_t st = correct(c, 2, ms);
           if (st != hipSuccess) return st;
-          if (ms < tc) {
-            tc = ms;
-            bc = cs;
-          }
+          corr.push_back({c, ms});
         }
       }
+  // Two launches differ by 2% from one another: the configurations within 3% of the best are timed
+  // again, four times as long (split BF16, 42 775 elements: 0.296 and 0.295 ms after two launches, in
+  // either order; 0.297 and 0.291 after eight, and 11.1 and 10.8 ms for a pass over the whole box).
+  auto best = [&](std::vector<Timed>& all, auto& time, LaunchCfg& c) {
+    auto less = [](const Timed& x, const Timed& y) { return x.ms < y.ms; };
+    const float lim = 1.03f * std::min_element(all.begin(), all.end(), less)->ms;
+    all.erase(std::remove_if(all.begin(), all.end(), [&](const Timed& x) { return x.ms > lim; }), all.end());
+    for (Timed& x : all) {
+      if (all.size() == 1) break;
+      const hipError_t st = time(x.c, 8, x.ms);
+      if (st != hipSuccess) return st;
+    }
+    c = std::min_element(all.begin(), all.end(), less)->c;
+    return hipSuccess;
+  };
+  LaunchCfg bp, bc;
+  hipError_t st = best(pred, predict, bp);
+  if (st == hipSuccess) st = best(corr, correct, bc);
+  if (st != hipSuccess) return st;
   t.pc = bp;
   t.cc = bc;
   t.source = 1;
