@@ -450,7 +450,8 @@ def launch_record(precision, inf):
             "predict_shape": {("fp32", 0): "I~ park LDS", ("fp32", 1): "I~ park HBM",
                               ("bf16", 0): "bf16 16x16x16", ("bf16", 1): "bf16 16x16x32",
                               ("bf16x3", 0): "split bf16 16x16x16"}.get(
-                                  (precision, inf["shape"]), "plain"),
+                                  (precision, inf["shape"]),
+                                  "fp64 groups" if inf["kernel"] == 0 and 3 <= inf["order"] <= 6 else "plain"),
             "source": ["default", "measured", "cache"][inf["launch_source"]]}
 
 

@@ -236,13 +236,10 @@ __global__ __launch_bounds__(NT_TALL) void k_predict_plain(DevData<T> d, int64_t
     __syncthreads();
   }
   // traces at the face nodes: full step and first half step
-  if constexpr (kOneItem<N>) {
+  if (single) {
     plain_trace<1, T, N>(d, finer ? 2 : 1, sI, sV, sIh, sVh);
   } else {  // one set fills the threads
-    if (single)
-      plain_trace<1, T, N>(d, 1, sI, sV, sI, sV);
-    else
-      plain_trace<2, T, N>(d, 1, sI, sV, sI, sV);
+    plain_trace<2, T, N>(d, 1, sI, sV, sI, sV);
     if (finer) plain_trace<2, T, N>(d, 1, sIh, sVh, sIh, sVh);
   }
   __syncthreads();
