@@ -36,22 +36,28 @@ void element_map(const Model& M, int64_t e, double x0[3], double Ji[9]) {
 
 // A sample is bound by the rows of the tiled state (and their pages) that a
 // load touches, and, for few points, by the wavefronts that share them out.
-// Two forms; every sum runs over the modes in ascending order in both.
+// Three forms; every sum runs over the modes in ascending order in all of them.
 //
-// A thread per (point, quantity): 16 points by nine quantities per 144 threads.
-// Scattered receivers at order 6 in FP32, 256 / 4096 / 16 384 of them: 7 / 18 /
-// 61 us, with a thread per point 126 / 127 / 132 (64 rows and pages a load, a
-// ninth of the wavefronts).
-template <typename T>
+// A thread per (point, quantity), 16 points by nine quantities per 144 threads
+// and eight modes' loads in flight. Scattered receivers at order 6 in FP32, 256 /
+// 4096 of them: 7 / 18 us, with a thread per point 126 / 127 (64 rows and pages a
+// load, a ninth of the wavefronts).
+//
+// DENSE, for thousands of scattered points: a point's nine threads side by side and
+// a mode a trip. The wavefronts then walk the modes nearly in step, and a row is
+// still in the L2 when the next receiver of its 16 elements asks for it: 16 384
+// receivers in a box of 24 000 tets, FP64 order 6, fetch 288 MB in 84 us (431 MB in
+// 129 with the form above); FP32 51 us (59).
+template <typename T, bool DENSE>
 __global__ __launch_bounds__(192) void k_sample(const T* Q, int RT, int B, const int32_t* elem, const double* phi,
                                                int64_t n, double* out, const double* eta, double* eta_out) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x, c = i / 144;
-  const int j = int(i - c * 144), p = j >> 4;
-  const int64_t r = c * 16 + (j & 15);
+  const int j = int(i - c * 144), p = DENSE ? int(i % 9) : j >> 4;
+  const int64_t r = DENSE ? i / 9 : c * 16 + (j & 15);
   if (r >= n) return;
   const T* q = Q + qidx(elem[r], 0, p, RT);
   double acc = 0.0;
-#pragma unroll 8
+#pragma unroll(DENSE ? 1 : 8)
   for (int l = 0; l < B; ++l) acc += phi[l * n + r] * (double)q[(l >> 2) * 576 + (l & 3) * 16];
   out[r * 9 + p] = acc;
   if (p == 0 && eta_out) eta_out[r] = eta[r];
@@ -244,16 +250,21 @@ hipError_t launch_sample(const PointSet& ps, int B, const double* Q64, const flo
   // rows are whole cache lines, from 32 768 on in any order. Thread per point / per sum:
   // centroids of graded boxes, FP64 order 5, 23 562: 25 / 39 us, FP32 order 6, 72 576: 60 / 77;
   // of regular boxes, FP32 order 6, 16 384: 21 / 16, 24 000: 16 / 13, 192 000: 99 / 133; scattered,
-  // FP32, 16 384: 208 / 79, 100 000: 589 / 463, FP64, 16 384: 167 / 124, 24 000: 170 / 187, 100 000: 429 / 763.
+  // FP32, 16 384: 208 / 51, 100 000: 589 / 341, FP64, 16 384: 167 / 84, 24 000: 170 / 107, 48 000: 173 / 333.
   // Work-groups of a wavefront below 4096 points, where they reach more CUs (1024 points 7.5 us, 11 with
   // three), of three above (4096 points 18 us, 20 with one).
   const bool wide = ps.n >= (ps.ordered ? 20480 : 32768) && (ps.ordered || Q64);
+  // The dense form for scattered points from 6144 on: dense / 16 by nine at order 6, 4096 points 24 / 19 us
+  // (FP32), 34 / 35 (FP64), 6144: 27 / 32, 47 / 59, 100 000: 341 / 384 (FP32). In mesh order, where
+  // 16 points read the same lines, it is slower at every size (4096 points, FP32: 22 / 12 us).
+  const bool dense = !ps.ordered && ps.n >= 6144;
   const int64_t threads = wide ? ps.n : (ps.n + 15) / 16 * 144;
-  const int wg = wide ? 256 : (ps.n < 4096 ? 64 : 192);
+  const int wg = wide ? 256 : (dense || ps.n < 4096 ? 64 : 192);
   auto launch = [&](const auto* Q) {
     using T = std::remove_const_t<std::remove_reference_t<decltype(*Q)>>;
-    hipLaunchKernelGGL(wide ? k_sample_wide<T> : k_sample<T>, dim3((unsigned)((threads + wg - 1) / wg)), dim3(wg), 0, s,
-                       Q, RT, B, ps.elem, ps.phi, ps.n, out, eta, eta_out);
+    auto* k = wide ? k_sample_wide<T> : dense ? k_sample<T, true> : k_sample<T, false>;
+    hipLaunchKernelGGL(k, dim3((unsigned)((threads + wg - 1) / wg)), dim3(wg), 0, s, Q, RT, B, ps.elem, ps.phi,
+                       ps.n, out, eta, eta_out);
   };
   if (Q64)
     launch(Q64);
